@@ -44,6 +44,14 @@ bool use_onchip(const ldpc_graph &g, uint32_t flags) {
     return ldpc::onchip_fits(g);
 }
 
+// Where the on-chip path does not apply: the LDS-resident decoder for graphs
+// that it takes, unless streaming is forced or chosen by the tuning record.
+bool use_lds(const ldpc_graph &g, uint32_t flags) {
+    if (flags & LDPC_FORCE_STREAM) return false;
+    if (g.tuning.set && g.tuning.path == 2 && !g.tuning.lds) return false;
+    return ldpc::lds_fits(g);
+}
+
 int decode(const ldpc_graph *g, const float *llr, int32_t B, int32_t L, uint32_t flags, const float *alpha,
            const float *beta, int32_t T, uint8_t *bits, float *post, int32_t *iters, uint8_t *ok, void *ws,
            size_t ws_bytes, hipStream_t stream) {
@@ -56,6 +64,8 @@ int decode(const ldpc_graph *g, const float *llr, int32_t B, int32_t L, uint32_t
         if (!ldpc::onchip_fits(*g)) return LDPC_EUNSUPPORTED;
         return ldpc::onchip_decode(*g, llr, B, L, flags, alpha, beta, T, bits, post, iters, ok, ws, ws_bytes, stream);
     }
+    if (use_lds(*g, flags))
+        return ldpc::lds_decode(*g, llr, B, L, flags, alpha, beta, bits, post, iters, ok, ws, ws_bytes, stream);
     return ldpc::stream_decode(*g, llr, B, L, flags, alpha, beta, T, bits, post, iters, ok, ws, ws_bytes, stream);
 }
 

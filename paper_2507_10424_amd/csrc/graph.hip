@@ -167,6 +167,13 @@ void free_graph_arrays(ldpc_graph *g) {
     (void)hipFree(g->cf.bitpos);
     (void)hipFree(g->cf.slot_bit);
     (void)hipFree(g->cf.row_class);
+    (void)hipFree(g->lds.rows);
+    (void)hipFree(g->lds.bits);
+    (void)hipFree(g->lds.row_group);
+    (void)hipFree(g->lds.bit_group);
+    (void)hipFree(g->lds.slot_of);
+    (void)hipFree(g->lds.row_class);
+    g->lds = {};
     (void)hipFree(g->stream_order.col_idx);
     (void)hipFree(g->stream_order.csc_edge);
     (void)hipFree(g->stream_order.row_class);
@@ -336,6 +343,32 @@ int build(const uint8_t *H, int32_t m, int32_t n, hipStream_t s, ldpc_graph *g) 
                 g->cf.cpt = lay.cpt;
                 g->cf.dvs = lay.dv;
                 g->cf.dvp = lay.dvp;
+            }
+        }
+        // The LDS-resident decoder's tables, for graphs that no on-chip variant takes.
+        if (E > 0 && n < 65536 && E < 65536 && !ldpc::onchip_fits(*g)) {
+            std::vector<int32_t> h_bit(E);
+            if (hipMemcpy(h_bit.data(), g->col_idx, sizeof(int32_t) * E, hipMemcpyDeviceToHost) != hipSuccess) {
+                fail(LDPC_EHIP);
+                break;
+            }
+            ldpc_graph &G = *g;
+            LdsHostTables T;
+            auto up = [&](auto **dst, const auto &v) {
+                using X = std::remove_reference_t<decltype(v[0])>;
+                if (dalloc(dst, v.size()) != hipSuccess) return fail(LDPC_ENOMEM);
+                if (!v.empty() && hipMemcpy(*dst, v.data(), sizeof(X) * v.size(), hipMemcpyHostToDevice) != hipSuccess)
+                    return fail(LDPC_EHIP);
+                return (int)LDPC_OK;
+            };
+            if (ldpc::lds_tables(h_rowptr, h_bit, h_class, m, n, &T)) {
+                G.lds.row_groups = (int32_t)T.row_group.size();
+                G.lds.bit_groups = (int32_t)T.bit_group.size();
+                G.lds.npos = T.npos;
+                if (up(&G.lds.rows, T.rows) || up(&G.lds.bits, T.bits) || up(&G.lds.row_group, T.row_group) ||
+                    up(&G.lds.bit_group, T.bit_group) || up(&G.lds.slot_of, T.slot_of) ||
+                    up(&G.lds.row_class, T.row_class))
+                    break;
             }
         }
         // Row order of the streaming path, where its check kernel reads

@@ -11,6 +11,29 @@
 
 #include "ldpc.h"
 
+// Tables of the LDS-resident decoder (decode_lds.hip): rows and bits in groups
+// of 64 of one (padded) degree.
+struct LdsGroup {
+    int32_t degree; // neighbours listed per row (bit)
+    int32_t first;  // rows: position of the first message
+    int32_t table;  // first word of the group's index pairs: word k of lane l at table + 64 k + l
+    int32_t pad;
+};
+struct LdsTables {
+    const uint32_t *rows, *bits; // pairs of posterior slots / of message positions
+    const LdsGroup *row_group, *bit_group;
+    const uint16_t *slot_of;  // n: posterior slot of each bit
+    const int32_t *row_class; // degree class per row slot
+    int32_t row_groups, bit_groups, npos;
+};
+struct LdsHostTables {
+    std::vector<uint32_t> rows, bits;
+    std::vector<LdsGroup> row_group, bit_group;
+    std::vector<uint16_t> slot_of;
+    std::vector<int32_t> row_class;
+    int32_t npos = 0; // message positions; position npos holds 0
+};
+
 // Device-side Tanner graph.  Edges are numbered row by row (CSR order), bits
 // ascending inside a row; the CSC side lists, for every bit, the CSR numbers
 // of its edges in ascending check index.
@@ -43,6 +66,15 @@ struct ldpc_graph {
         int32_t rpt = 0, cpt = 0, dvs = 0; // rows and bits per thread, bit-side stride
         uint32_t dvp = 0;                  // column degree profile, 0 none
     } cf;
+    // LDS-resident decoder: its tables (LdsTables), built for graphs that no
+    // on-chip variant fits and whose rows have at most 32 edges; null otherwise.
+    struct {
+        uint32_t *rows = nullptr, *bits = nullptr;
+        LdsGroup *row_group = nullptr, *bit_group = nullptr;
+        uint16_t *slot_of = nullptr;
+        int32_t *row_class = nullptr;
+        int32_t row_groups = 0, bit_groups = 0, npos = 0;
+    } lds;
     // Streaming path, for graphs of one row degree (6 or 7) whose tile of
     // posteriors exceeds an L2: the rows renumbered in a cache-friendly order
     // (stream_row_order), so that the check kernel's launch order follows it
@@ -63,6 +95,7 @@ struct ldpc_graph {
     struct {
         bool set = false;
         int path = 0;         // 1 on-chip, 2 streaming
+        bool lds = false;     // path 2 from the autotuner, but the LDS-resident decoder was faster
         int variant = -1;     // on-chip kernel variant
         int wg_per_cu = 0;    // on-chip workgroups per CU (0: occupancy limit)
         int waves_per_simd = 0; // on-chip register budget: 0 compiler's, 4 / 3 at least 4 / 3 waves per SIMD
@@ -129,6 +162,18 @@ bool onchip_cf_layout(const std::vector<int32_t> &rowptr, const std::vector<int3
 // profile; false if none fits.
 bool onchip_cf_geometry(const ldpc_graph &g, const std::vector<int32_t> &col_deg, int32_t *rpt, int32_t *cpt,
                         int32_t *dvs, uint32_t *dvp);
+
+// LDS-resident decoder for other codes whose state fits one CU: its tables
+// (false if the graph is out of its range), whether it takes the graph, launch
+// (the workspace is the streaming path's).
+constexpr int kLdsMaxThreads = 1024; // of a workgroup
+constexpr int kLdsMaxDegree = 32;    // of a row
+bool lds_tables(const std::vector<int32_t> &rowptr, const std::vector<int32_t> &col,
+                const std::vector<int32_t> &row_class, int32_t m, int32_t n, LdsHostTables *out);
+bool lds_fits(const ldpc_graph &g);
+int lds_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, uint32_t flags, const float *alpha,
+               const float *beta, uint8_t *bits, float *post, int32_t *iters, uint8_t *ok, void *ws, size_t ws_bytes,
+               hipStream_t stream);
 
 // Order of the rows for the streaming check kernel (roworder.hip): a
 // permutation of 0 .. m-1 that keeps rows sharing bits close together.
