@@ -269,9 +269,13 @@ int ldpc_nms_decode(const ldpc_graph *g, const float *llr_dev, int32_t B, int32_
  * the binary cross-entropy of every iteration's posterior against the
  * transmitted bits c (P(bit = 1) = sigmoid(-s)).
  *
- * ldpc_nms_train_workspace_bytes: workspace for B frames, T iterations and a
- * checkpoint of the decoder state every `ckpt_every` iterations (the
- * forward's checkpoints stay there for the backward).
+ * ldpc_nms_train_workspace_bytes: workspace for B frames and T iterations.  It
+ * keeps, of every iteration, each row's two smallest magnitudes, their
+ * positions and the signs (12 bytes, 16 and more for rows of more than 16
+ * edges) and each bit's posterior for the backward, as long as all frames'
+ * take at most 8 GiB, or at most what a checkpoint of the messages and
+ * posteriors every `ckpt_every` iterations would take; beyond that the batch
+ * is trained in passes and the backward runs the forward of each pass again.
  *
  * ldpc_nms_train_forward: runs the T iterations with the weights (alpha_dev,
  * beta_dev: T x n_classes float32, device), writes the mean loss to
@@ -282,16 +286,15 @@ int ldpc_nms_decode(const ldpc_graph *g, const float *llr_dev, int32_t B, int32_
  *
  * ldpc_nms_train_backward: gradient of grad_loss * loss with respect to alpha
  * and beta (written to galpha_dev, gbeta_dev, T x n_classes) and, if
- * gllr_dev is non-null, to the channel LLRs (B x n).  It reads the
- * checkpoints of the last forward call on the same workspace and inputs and
- * recomputes each segment of ckpt_every iterations.  The derivative of a
+ * gllr_dev is non-null, to the channel LLRs (B x n).  It reads what the last
+ * forward call on the same workspace and inputs kept.  The derivative of a
  * check message's magnitude goes to the edge attaining the minimum over the
  * row's other edges (lowest position on a tie), the sign product is held
  * constant and the clip max(v, 0) passes the gradient where v > 0.  Sums over
  * frames are taken in a fixed order (deterministic).
  *
- * The per-frame state lives in LDS when it fits one workgroup; otherwise it
- * lives in the workspace (4 n + 2 E + ckpt_every (n + E) floats per frame).
+ * The state lives in LDS when a frame's fits one workgroup (rows of at most 32
+ * edges); otherwise in the workspace, in tiles of 64 frames.
  * Errors: LDPC_EINVAL (null pointers, B, T or ckpt_every < 1),
  * LDPC_EWORKSPACE, LDPC_EUNSUPPORTED (more than 8 degree classes),
  * LDPC_EHIP.

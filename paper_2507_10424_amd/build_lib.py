@@ -40,10 +40,10 @@ HIPCC_FLAGS = [
 ]
 
 
-# Flags of single sources.  decode_lds.hip: the arrays of its unrolled rows stay
+# Flags of single sources.  The arrays of their unrolled rows stay
 # scalars; turned into vectors of up to 32 registers, every write of an element
 # copies the vector, and the kernels for rows of 32 spill 2 KB instead of 12 bytes.
-FILE_FLAGS = {"decode_lds.hip": ["-mllvm", "-disable-promote-alloca-to-vector"]}
+FILE_FLAGS = {f: ["-mllvm", "-disable-promote-alloca-to-vector"] for f in ("decode_lds.hip", "train_lds.hip")}
 
 # what the host pass prints for the device-only target feature (see above)
 HOST_FEATURE_NOTICE = "'-packed-fp32-ops' is not a recognized feature for this target (ignoring feature)"

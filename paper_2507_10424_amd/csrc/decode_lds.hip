@@ -31,6 +31,7 @@
 #include <algorithm>
 
 #include "ldpc_internal.h"
+#include "lds_common.h"
 #include "minsum_row.h"
 
 namespace ldpc {
@@ -65,16 +66,6 @@ struct LdsJob {
     uint32_t *queue; // frames taken beyond the grid's first ones (zero before the launch), or null: none left
 };
 
-template <class V> __device__ __forceinline__ V ld(const unsigned char *lds, uint32_t off) {
-    return *reinterpret_cast<const V *>(lds + off);
-}
-template <class V> __device__ __forceinline__ void st(unsigned char *lds, uint32_t off, V v) {
-    *reinterpret_cast<V *>(lds + off) = v;
-}
-__device__ __forceinline__ uint32_t half_of(const uint32_t *w, int k) {
-    return (k & 1) ? w[k >> 1] >> 16 : w[k >> 1] & 0xffffu;
-}
-
 // The rows of one group: `held` their bits' slots in registers, or `tab`
 // (non-null) where to read them; `ea` the LDS address of the lane's first
 // message.  al, be: the rows' weights per slot (NMS).
@@ -102,10 +93,10 @@ __device__ __forceinline__ void check_rows(unsigned char *lds, const uint32_t *h
         V sv[kStep], ev[kStep];
 #pragma unroll
         for (int k = 0; k < kStep; ++k)
-            if (k0 + k < DC) sv[k] = ld<V>(lds, kEnt * half_of(w, k0 + k));
+            if (k0 + k < DC) sv[k] = lds_get<V>(lds, kEnt * half_of(w, k0 + k));
 #pragma unroll
         for (int k = 0; k < kStep; ++k)
-            if (k0 + k < DC) ev[k] = ld<V>(lds, ea + 64u * kEnt * (uint32_t)(k0 + k));
+            if (k0 + k < DC) ev[k] = lds_get<V>(lds, ea + 64u * kEnt * (uint32_t)(k0 + k));
 #pragma unroll
         for (int k = 0; k < kStep; ++k)
             if (k0 + k < DC) {
@@ -145,7 +136,7 @@ __device__ __forceinline__ void check_rows(unsigned char *lds, const uint32_t *h
         }
     }
 #pragma unroll
-    for (int k = 0; k < DC; ++k) st<V>(lds, ea + 64u * kEnt * (uint32_t)k, x[k]);
+    for (int k = 0; k < DC; ++k) lds_put<V>(lds, ea + 64u * kEnt * (uint32_t)k, x[k]);
     asm volatile("; end of rows of %0" ::"n"(DC));
 }
 
@@ -240,19 +231,19 @@ __global__ __launch_bounds__(kMaxThreads) void k_lds(const LdsJob J, int32_t L, 
 #pragma unroll
             for (int q = 0; q < F; ++q)
                 v[q] = fr[q] < B ? llr[(size_t)fr[q] * n + j] + 0.0f : 0.0f; // -0 -> +0
-            st<V>(lds, kEnt * slot_of[j], v);
+            lds_put<V>(lds, kEnt * slot_of[j], v);
         }
     }
     if (tid == 0) {
-        st<V>(lds, kEnt * (uint32_t)n, V(__builtin_inff()));
-        st<V>(lds, zero_at, V(0.0f));
+        lds_put<V>(lds, kEnt * (uint32_t)n, V(__builtin_inff()));
+        lds_put<V>(lds, zero_at, V(0.0f));
     }
-    for (int32_t e = tid; e < J.t.npos; e += nt) st<V>(lds, eta0 + kEnt * (uint32_t)e, V(0.0f));
+    for (int32_t e = tid; e < J.t.npos; e += nt) lds_put<V>(lds, eta0 + kEnt * (uint32_t)e, V(0.0f));
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
         const int32_t p = tid + c * nt;
-        if (p < n) rc[c] = ld<V>(lds, kEnt * (uint32_t)p);
+        if (p < n) rc[c] = lds_get<V>(lds, kEnt * (uint32_t)p);
     }
     uint32_t pend = (1u << F) - 1u; // slots whose next frame's LLRs are to be read
 
@@ -346,7 +337,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_lds(const LdsJob J, int32_t L, 
             for (int c = 0; c < CPT; ++c) {
                 const int32_t j = tr + c * nt;
                 if (j < n) {
-                    const float v = ld<V>(lds, kEnt * slot_of[j])[q];
+                    const float v = lds_get<V>(lds, kEnt * slot_of[j])[q];
                     if (J.post) J.post[o + j] = v;
                     J.bits[o + j] = v < 0.0f ? 1 : 0;
                 }
@@ -387,7 +378,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_lds(const LdsJob J, int32_t L, 
             const int32_t g = w + c * nw;
             if (g < J.t.bit_groups) {
                 V acc = 0.0f;
-                auto msg = [&](uint32_t h) { return ld<V>(lds, eta0 + kEnt * h); };
+                auto msg = [&](uint32_t h) { return lds_get<V>(lds, eta0 + kEnt * h); };
                 const int32_t d = bdeg[c];
                 if (kBitWords >= 2 && d == 3) {
                     const V a = msg(half_of(bw[c], 0)), b = msg(half_of(bw[c], 1)), e = msg(half_of(bw[c], 2));
@@ -418,7 +409,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_lds(const LdsJob J, int32_t L, 
                     }
                 }
                 const int32_t s = g * 64 + lr;
-                if (s < n) st<V>(lds, kEnt * (uint32_t)s, acc + rc[c]);
+                if (s < n) lds_put<V>(lds, kEnt * (uint32_t)s, acc + rc[c]);
             }
         }
         if (fin) { // the new frames start from s = r and messages of 0
@@ -429,9 +420,9 @@ __global__ __launch_bounds__(kMaxThreads) void k_lds(const LdsJob J, int32_t L, 
 #pragma unroll
                 for (int c = 0; c < CPT; ++c) {
                     const int32_t j = tr + c * nt;
-                    if (j < n) st<float>(lds, kEnt * slot_of[j] + 4u * (uint32_t)q, fr[q] < B ? rnx[c][q] + 0.0f : 0.0f);
+                    if (j < n) lds_put<float>(lds, kEnt * slot_of[j] + 4u * (uint32_t)q, fr[q] < B ? rnx[c][q] + 0.0f : 0.0f);
                 }
-                for (int32_t e = tr; e < J.t.npos; e += nt) st<float>(lds, eta0 + kEnt * (uint32_t)e + 4u * (uint32_t)q, 0.0f);
+                for (int32_t e = tr; e < J.t.npos; e += nt) lds_put<float>(lds, eta0 + kEnt * (uint32_t)e + 4u * (uint32_t)q, 0.0f);
             }
             __syncthreads();
 #pragma unroll
@@ -440,7 +431,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_lds(const LdsJob J, int32_t L, 
                 if (s < n) {
 #pragma unroll
                     for (int q = 0; q < F; ++q)
-                        if ((fin >> q) & 1u) rc[c][q] = ld<float>(lds, kEnt * (uint32_t)s + 4u * (uint32_t)q);
+                        if ((fin >> q) & 1u) rc[c][q] = lds_get<float>(lds, kEnt * (uint32_t)s + 4u * (uint32_t)q);
                 }
             }
             pend = fin;
@@ -501,8 +492,8 @@ int lds_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, uint
     const int64_t room = (int64_t)std::max(per_cu, 1) * g.num_cu, groups = ((int64_t)B + F - 1) / F;
     const int grid = (int)std::min(room, groups);
     LdsJob J{};
-    J.t = LdsTables{g.lds.rows, g.lds.bits, g.lds.row_group, g.lds.bit_group, g.lds.slot_of, g.lds.row_class,
-                    g.lds.row_groups, g.lds.bit_groups, g.lds.npos};
+    J.t = LdsTables{g.lds.rows, g.lds.bits, g.lds.row_group, g.lds.bit_group, g.lds.slot_of, g.lds.bit_of,
+                    g.lds.row_class, g.lds.row_groups, g.lds.bit_groups, g.lds.npos};
     J.n = g.n;
     J.llr = llr;
     J.B = B;

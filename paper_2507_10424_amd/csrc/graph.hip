@@ -172,6 +172,7 @@ void free_graph_arrays(ldpc_graph *g) {
     (void)hipFree(g->lds.row_group);
     (void)hipFree(g->lds.bit_group);
     (void)hipFree(g->lds.slot_of);
+    (void)hipFree(g->lds.bit_of);
     (void)hipFree(g->lds.row_class);
     g->lds = {};
     (void)hipFree(g->stream_order.col_idx);
@@ -345,8 +346,8 @@ int build(const uint8_t *H, int32_t m, int32_t n, hipStream_t s, ldpc_graph *g) 
                 g->cf.dvp = lay.dvp;
             }
         }
-        // The LDS-resident decoder's tables, for graphs that no on-chip variant takes.
-        if (E > 0 && n < 65536 && E < 65536 && !ldpc::onchip_fits(*g)) {
+        // The tables of the LDS-resident decoder and training.
+        if (E > 0 && n < 65536 && E < 65536) {
             std::vector<int32_t> h_bit(E);
             if (hipMemcpy(h_bit.data(), g->col_idx, sizeof(int32_t) * E, hipMemcpyDeviceToHost) != hipSuccess) {
                 fail(LDPC_EHIP);
@@ -367,7 +368,7 @@ int build(const uint8_t *H, int32_t m, int32_t n, hipStream_t s, ldpc_graph *g) 
                 G.lds.npos = T.npos;
                 if (up(&G.lds.rows, T.rows) || up(&G.lds.bits, T.bits) || up(&G.lds.row_group, T.row_group) ||
                     up(&G.lds.bit_group, T.bit_group) || up(&G.lds.slot_of, T.slot_of) ||
-                    up(&G.lds.row_class, T.row_class))
+                    up(&G.lds.bit_of, T.bit_of) || up(&G.lds.row_class, T.row_class))
                     break;
             }
         }

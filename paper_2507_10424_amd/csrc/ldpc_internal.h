@@ -11,7 +11,8 @@
 
 #include "ldpc.h"
 
-// Tables of the LDS-resident decoder (decode_lds.hip): rows and bits in groups
+// Tables of the LDS-resident decoder and training (decode_lds.hip,
+// train_lds.hip): rows and bits in groups
 // of 64 of one (padded) degree.
 struct LdsGroup {
     int32_t degree; // neighbours listed per row (bit)
@@ -23,13 +24,14 @@ struct LdsTables {
     const uint32_t *rows, *bits; // pairs of posterior slots / of message positions
     const LdsGroup *row_group, *bit_group;
     const uint16_t *slot_of;  // n: posterior slot of each bit
+    const uint16_t *bit_of;   // n: bit of each posterior slot
     const int32_t *row_class; // degree class per row slot
     int32_t row_groups, bit_groups, npos;
 };
 struct LdsHostTables {
     std::vector<uint32_t> rows, bits;
     std::vector<LdsGroup> row_group, bit_group;
-    std::vector<uint16_t> slot_of;
+    std::vector<uint16_t> slot_of, bit_of;
     std::vector<int32_t> row_class;
     int32_t npos = 0; // message positions; position npos holds 0
 };
@@ -66,12 +68,12 @@ struct ldpc_graph {
         int32_t rpt = 0, cpt = 0, dvs = 0; // rows and bits per thread, bit-side stride
         uint32_t dvp = 0;                  // column degree profile, 0 none
     } cf;
-    // LDS-resident decoder: its tables (LdsTables), built for graphs that no
-    // on-chip variant fits and whose rows have at most 32 edges; null otherwise.
+    // LDS-resident decoder and training: their tables (LdsTables), for graphs
+    // whose rows have at most 32 edges; null otherwise.
     struct {
         uint32_t *rows = nullptr, *bits = nullptr;
         LdsGroup *row_group = nullptr, *bit_group = nullptr;
-        uint16_t *slot_of = nullptr;
+        uint16_t *slot_of = nullptr, *bit_of = nullptr;
         int32_t *row_class = nullptr;
         int32_t row_groups = 0, bit_groups = 0, npos = 0;
     } lds;

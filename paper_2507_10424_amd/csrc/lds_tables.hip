@@ -1,5 +1,5 @@
-// Tables of the LDS-resident decoder (decode_lds.hip), host code run once per
-// graph at build time.
+// Tables of the LDS-resident decoder and training (decode_lds.hip,
+// train_lds.hip), host code run once per graph at build time.
 //
 // Rows and bits are sorted by degree (stable, descending) and cut into groups
 // of 64, one lane each.  A group of rows lists the posterior slots of its
@@ -39,7 +39,11 @@ bool lds_tables(const std::vector<int32_t> &rowptr, const std::vector<int32_t> &
     std::stable_sort(bits.begin(), bits.end(), [&](int32_t a, int32_t b) { return cdeg(a) > cdeg(b); });
     LdsHostTables T;
     T.slot_of.resize(n);
-    for (int32_t p = 0; p < n; ++p) T.slot_of[bits[p]] = (uint16_t)p;
+    T.bit_of.resize(n);
+    for (int32_t p = 0; p < n; ++p) {
+        T.slot_of[bits[p]] = (uint16_t)p;
+        T.bit_of[p] = (uint16_t)bits[p];
+    }
     // rows: groups of 64, positions group by group
     std::vector<int32_t> edge_pos(col.size());
     const int32_t rg = ((int32_t)rows.size() + 63) / 64;

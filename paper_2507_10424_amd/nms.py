@@ -18,8 +18,7 @@ class NMSLoss(torch.autograd.Function):
 
     Mean over frames and bits of sum_{t=1..T} softplus((2c - 1) s^(t)), T =
     alpha.shape[0].  Backward gives d loss / d alpha, d beta and d llr from the
-    hand-written reverse sweep (recomputing every ckpt_every iterations from
-    checkpoints kept in `workspace`)."""
+    hand-written reverse sweep over what the forward kept in `workspace`."""
 
     @staticmethod
     def forward(ctx, alpha, beta, llr, graph, ckpt_every, workspace, target=None):
