@@ -17,6 +17,76 @@ namespace {
 // The row degree that the kernel unrolls for a group whose largest row has d edges.
 int row_bucket(int d) { return d <= 2 ? 2 : d <= 16 ? d : (d + 3) / 4 * 4; }
 
+// Chooses which bit of a degree sits in which slot.  A wavefront gathers, per
+// edge number k, the posteriors of 64 rows and, per column entry u, the
+// messages of 64 bits; the LDS serves 32 lanes at a time without conflict when
+// their words differ modulo 32 (a message's word is its row's lane modulo 32).
+// Random swaps of two bits of one degree are kept while they lower the sum over
+// the 32-lane halves of the squared numbers of lanes per bank.  Rows keep their
+// lanes and their edges' order (training breaks ties by it).
+void spread_banks(const std::vector<int32_t> &rowptr, const std::vector<int32_t> &col, const std::vector<int32_t> &rows,
+                  const std::vector<int32_t> &colptr, std::vector<int32_t> &bits) {
+    constexpr int kBanks = 32, kTrials = 48; // trials per bit: 1 to 60 ms for the codes in range
+    const int32_t n = (int32_t)bits.size();
+    if (n < 2) return;
+    // of every bit's messages, by ascending check: the half of rows and edge number, and the row's lane
+    struct Use {
+        int32_t hist; // first bin of (row half, k)
+        int32_t lane;
+    };
+    std::vector<int32_t> place(rowptr.size(), -1);
+    for (size_t p = 0; p < rows.size(); ++p) place[rows[p]] = (int32_t)p;
+    std::vector<Use> use(col.size());
+    std::vector<int32_t> fill(colptr.begin(), colptr.end() - 1);
+    const size_t halves = (rows.size() + 31) / 32;
+    for (size_t i = 0; i + 1 < rowptr.size(); ++i)
+        for (int32_t e = rowptr[i]; e < rowptr[i + 1]; ++e)
+            use[fill[col[e]]++] = Use{(int32_t)(((size_t)place[i] / 32 * kLdsMaxDegree + (e - rowptr[i])) * kBanks),
+                                      place[i] % kBanks};
+    int32_t dv = 0;
+    for (int32_t j = 0; j < n; ++j) dv = std::max(dv, colptr[j + 1] - colptr[j]);
+    std::vector<int16_t> rh(halves * kLdsMaxDegree * kBanks, 0);               // check pass
+    std::vector<int16_t> bh((size_t)((n + 31) / 32) * std::max(dv, 1) * kBanks, 0); // bit pass
+    auto put = [&](int32_t j, int32_t p, int s) { // adds (takes) bit j at slot p; the change of the sums
+        int32_t d = 0;
+        for (int32_t q = colptr[j]; q < colptr[j + 1]; ++q) {
+            int16_t &a = rh[(size_t)use[q].hist + p % kBanks];
+            int16_t &b = bh[((size_t)(p / 32) * dv + (q - colptr[j])) * kBanks + use[q].lane];
+            d += 2 * s * (a + b) + 2;
+            a += (int16_t)s;
+            b += (int16_t)s;
+        }
+        return d;
+    };
+    for (int32_t p = 0; p < n; ++p) put(bits[p], p, 1);
+    uint32_t seed = 12345u;
+    auto rnd = [&](uint32_t below) {
+        seed = seed * 1664525u + 1013904223u;
+        return (int32_t)(((uint64_t)seed * below) >> 32);
+    };
+    for (int32_t lo = 0; lo < n;) { // the slots of one degree
+        int32_t hi = lo;
+        const int32_t d = colptr[bits[lo] + 1] - colptr[bits[lo]];
+        while (hi < n && colptr[bits[hi] + 1] - colptr[bits[hi]] == d) ++hi;
+        if (d > 0 && hi - lo > 1)
+            for (int64_t t = 0; t < (int64_t)kTrials * (hi - lo); ++t) {
+                const int32_t p = lo + rnd((uint32_t)(hi - lo)), q = lo + rnd((uint32_t)(hi - lo));
+                if (p == q) continue;
+                const int32_t a = bits[p], b = bits[q];
+                const int32_t change = put(a, p, -1) + put(b, q, -1) + put(a, q, 1) + put(b, p, 1);
+                if (change <= 0) {
+                    std::swap(bits[p], bits[q]);
+                } else {
+                    put(a, q, -1);
+                    put(b, p, -1);
+                    put(a, p, 1);
+                    put(b, q, 1);
+                }
+            }
+        lo = hi;
+    }
+}
+
 } // namespace
 
 bool lds_tables(const std::vector<int32_t> &rowptr, const std::vector<int32_t> &col,
@@ -37,6 +107,7 @@ bool lds_tables(const std::vector<int32_t> &rowptr, const std::vector<int32_t> &
     std::iota(bits.begin(), bits.end(), 0);
     auto cdeg = [&](int32_t j) { return colptr[j + 1] - colptr[j]; };
     std::stable_sort(bits.begin(), bits.end(), [&](int32_t a, int32_t b) { return cdeg(a) > cdeg(b); });
+    spread_banks(rowptr, col, rows, colptr, bits);
     LdsHostTables T;
     T.slot_of.resize(n);
     T.bit_of.resize(n);

@@ -101,6 +101,22 @@ int main() {
         }
     }
     if (listed != col.size()) return fail("bit lists incomplete");
-    std::printf("ok\n");
+    // mean largest number of lanes per bank over the 32-lane halves of both passes' gathers
+    double load = 0.0, gathers = 0.0;
+    auto half = [&](const std::vector<uint32_t> &t, const LdsGroup &G, int h, int k, int none, int base) {
+        int bank[32] = {}, most = 0;
+        for (int l = 32 * h; l < 32 * h + 32; ++l) {
+            const int p = entry(t, G.table, k, l);
+            if (p != none) most = std::max(most, ++bank[(p - base) % 32]);
+        }
+        if (most) load += most, gathers += 1.0;
+    };
+    for (const LdsGroup &G : T.row_group)
+        for (int h = 0; h < 2; ++h)
+            for (int k = 0; k < G.degree; ++k) half(T.rows, G, h, k, n, 0);
+    for (const LdsGroup &G : T.bit_group)
+        for (int h = 0; h < 2; ++h)
+            for (int u = 0; u < G.degree; ++u) half(T.bits, G, h, u, T.npos, 0);
+    std::printf("ok %.3f\n", load / gathers);
     return 0;
 }

@@ -47,7 +47,10 @@ def codes():
 
 @pytest.mark.parametrize("name,H", list(codes()), ids=lambda v: v if isinstance(v, str) else "")
 def test_tables(checker, name, H):
-    assert run(checker, H) == "ok"
+    out = run(checker, H).split()
+    assert out[0] == "ok"
+    # lanes on the busiest bank of a 32-lane gather: 3.5 for random slots, 1 at best
+    assert float(out[1]) <= 3.0
 
 
 def test_out_of_range_graphs_are_refused(checker):
