@@ -331,12 +331,13 @@ int ldpc_adam_step(float *param_dev, const float *grad_dev, float *m1_dev, float
 
 /*
  * Launch choices of a graph ("tuning record").  Without one, decoding takes
- * the on-chip path whenever the graph fits (the preferred fitting kernel
- * variant: exact degrees, then the tightest degree masks, two frame slots;
- * as many workgroups as fit on each CU), else the LDS-resident decoder for
- * graphs whose n posteriors and E messages fit one CU's LDS with rows of at
- * most 32 edges (its workspace is the streaming path's), and otherwise the
- * streaming path with 4 wavefronts per workgroup.
+ * the on-chip path whenever the graph fits with rows of one degree (the
+ * preferred fitting kernel variant: exact degrees, then the tightest degree
+ * masks, two frame slots, one for small batches; as many workgroups as fit on
+ * each CU), else the LDS-resident decoder for graphs whose n posteriors and E
+ * messages fit one CU's LDS with rows of at most 32 edges (its workspace is
+ * the on-chip path's where the graph fits that, else the streaming path's),
+ * and otherwise the streaming path with 4 wavefronts per workgroup.
  *   path          1 on-chip, 2 streaming (0 in ldpc_graph_get_tuning: none set)
  *   variant       on-chip kernel variant (degree templates, rows and bits
  *                 per thread, frame slots), -1 for the preferred one
@@ -357,7 +358,7 @@ int ldpc_adam_step(float *param_dev, const float *grad_dev, float *m1_dev, float
  *                 (as many tiles as fit 200 MiB of posteriors, channel LLRs
  *                 and messages, at least one)
  * LDPC_FORCE_STREAM / LDPC_FORCE_ONCHIP still override the path, and a record
- * with path 2 that ldpc_graph_set_tuning set means the streaming kernels.
+ * that ldpc_graph_set_tuning set means the on-chip or streaming kernels.
  */
 typedef struct ldpc_tuning {
     int32_t path;
@@ -388,9 +389,10 @@ int ldpc_graph_get_tuning(const ldpc_graph *g, ldpc_tuning *t);
  * with 1, 2, 4, 8 wavefronts per workgroup, with and without non-temporal
  * message accesses, whole batch and chunks by size where those differ), times the four fastest again (three interleaved rounds
  * of four decodes), and stores the fastest of those in the graph's tuning
- * record (also returned in *best if non-null).  A graph of the LDS-resident
- * decoder gets its fastest streaming record, and keeps that decoder while the
- * record is set if it was faster than the record (best->ms is then its time).
+ * record (also returned in *best if non-null).  Where decoding
+ * without a record was faster still (the LDS-resident decoder, the one-slot
+ * kernels), the fastest record is kept and reported, with the faster time in
+ * best->ms, and the graph goes on decoding without it.
  * It synchronises `stream` and
  * creates two HIP events; do not capture it.  The workspace needs
  * ldpc_autotune_workspace_bytes(g, B) bytes.

@@ -76,7 +76,7 @@ extern "C" int ldpc_graph_set_tuning(ldpc_graph *g, const ldpc_tuning *t) {
     if (t->path == 1 && t->waves_per_simd != 0 && t->waves_per_simd != 3 && t->waves_per_simd != 4)
         return LDPC_EINVAL;
     g->tuning.set = true;
-    g->tuning.lds = false;
+    g->tuning.idle = false;
     g->tuning.path = t->path;
     g->tuning.variant = t->variant;
     g->tuning.wg_per_cu = t->wg_per_cu;
@@ -202,13 +202,15 @@ extern "C" int ldpc_autotune(ldpc_graph *g, int32_t B, int32_t max_iter, float e
             cands[best_k].ms = total[bq] / 3.0f;
         }
     }
-    // Graphs of the LDS-resident decoder: it has no choices to record, so the
-    // fastest streaming record stays beside a mark that it was faster.
-    bool lds = false;
-    if (st == LDPC_OK && best_k >= 0 && cands[best_k].path == 2 && lds_fits(*g)) {
+    // Decoding without a record can be faster still (the LDS-resident decoder,
+    // the one-slot kernels, which no record names): then the fastest record is
+    // kept, but lies idle.
+    bool idle = false;
+    if (st == LDPC_OK && best_k >= 0 && (onchip_fits(*g) || lds_fits(*g))) {
+        g->tuning.set = false;
         auto run = [&]() {
-            return lds_decode(*g, w.llr, B, max_iter, 0, nullptr, nullptr, w.bits, w.post, w.iters, w.ok, w.dec,
-                              w.dec_bytes, stream);
+            return ldpc_minsum_decode(g, w.llr, B, max_iter, 0, w.bits, w.post, w.iters, w.ok, w.dec, w.dec_bytes,
+                                      stream);
         };
         float ms = 0.0f;
         st = run();
@@ -217,8 +219,8 @@ extern "C" int ldpc_autotune(ldpc_graph *g, int32_t B, int32_t max_iter, float e
         if (st == LDPC_OK && (hipEventRecord(e1, stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                               hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
             st = LDPC_EHIP;
-        if (st == LDPC_OK && ms / 4 < cands[best_k].ms) {
-            lds = true;
+        if (st == LDPC_OK && ms / 4 < 0.97f * cands[best_k].ms) { // (by more than the runs differ)
+            idle = true;
             cands[best_k].ms = ms / 4;
         }
     }
@@ -229,7 +231,7 @@ extern "C" int ldpc_autotune(ldpc_graph *g, int32_t B, int32_t max_iter, float e
         return st ? st : LDPC_EHIP;
     }
     st = ldpc_graph_set_tuning(g, &cands[best_k]);
-    g->tuning.lds = lds;
+    g->tuning.idle = idle;
     if (best) *best = cands[best_k];
     return st;
 }

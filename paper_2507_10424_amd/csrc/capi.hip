@@ -40,16 +40,18 @@ int check_common(const ldpc_graph *g, const float *llr, int32_t B, int32_t L, ui
 bool use_onchip(const ldpc_graph &g, uint32_t flags) {
     if (flags & LDPC_FORCE_ONCHIP) return true;
     if (flags & LDPC_FORCE_STREAM) return false;
-    if (g.tuning.set && g.tuning.path == 2) return false;
+    if (g.tuned() && g.tuning.path == 2) return false;
     return ldpc::onchip_fits(g);
 }
 
-// Where the on-chip path does not apply: the LDS-resident decoder for graphs
-// that it takes, unless streaming is forced or chosen by the tuning record.
+// The LDS-resident decoder takes the graphs that it fits where the on-chip path
+// does not apply, and where that would mask every row to 8 or 16 edges (those
+// kernels carry every row's addresses in registers and spill: n = 500, rows of
+// 3 to 16, 500 frames: 0.449 ms on chip, 0.080 here), unless a flag or the
+// tuning record has chosen the path.
 bool use_lds(const ldpc_graph &g, uint32_t flags) {
-    if (flags & LDPC_FORCE_STREAM) return false;
-    if (g.tuning.set && g.tuning.path == 2 && !g.tuning.lds) return false;
-    return ldpc::lds_fits(g);
+    if (flags & (LDPC_FORCE_STREAM | LDPC_FORCE_ONCHIP)) return false;
+    return !g.tuned() && ldpc::lds_fits(g) && (!ldpc::onchip_fits(g) || ldpc::onchip_masks_rows(g));
 }
 
 int decode(const ldpc_graph *g, const float *llr, int32_t B, int32_t L, uint32_t flags, const float *alpha,
@@ -60,12 +62,15 @@ int decode(const ldpc_graph *g, const float *llr, int32_t B, int32_t L, uint32_t
     if ((flags & LDPC_FORCE_STREAM) && (flags & LDPC_FORCE_ONCHIP)) return LDPC_EINVAL;
     if (flags & ~ldpc::kKnownFlags) return LDPC_EINVAL;
     if (B == 0) return LDPC_OK;
+    if (use_lds(*g, flags)) {
+        // the workspace is the one that ldpc_decode_workspace_bytes asks for
+        if (ws == nullptr || ws_bytes < ldpc_decode_workspace_bytes(g, B, flags)) return LDPC_EWORKSPACE;
+        return ldpc::lds_decode(*g, llr, B, L, flags, alpha, beta, bits, post, iters, ok, ws, stream);
+    }
     if (use_onchip(*g, flags)) {
         if (!ldpc::onchip_fits(*g)) return LDPC_EUNSUPPORTED;
         return ldpc::onchip_decode(*g, llr, B, L, flags, alpha, beta, T, bits, post, iters, ok, ws, ws_bytes, stream);
     }
-    if (use_lds(*g, flags))
-        return ldpc::lds_decode(*g, llr, B, L, flags, alpha, beta, bits, post, iters, ok, ws, ws_bytes, stream);
     return ldpc::stream_decode(*g, llr, B, L, flags, alpha, beta, T, bits, post, iters, ok, ws, ws_bytes, stream);
 }
 

@@ -30,6 +30,7 @@
 // +infinity, which is never a row's minimum and never negative.
 #include <algorithm>
 
+#include "frame_queue.h"
 #include "ldpc_internal.h"
 #include "lds_common.h"
 #include "minsum_row.h"
@@ -50,6 +51,8 @@ template <> struct Vec<2> {
 struct Shared {
     int32_t next[2]; // each slot's frame after the current one
     uint32_t red[2]; // per-slot "a row is unsatisfied", by round parity
+    int32_t hc;      // thread 0: the counter it draws from,
+    uint32_t dead;   // and those found exhausted
 };
 
 struct LdsJob {
@@ -63,7 +66,8 @@ struct LdsJob {
     uint8_t *ok;
     const float *alpha, *beta; // T x ncls, or null
     int32_t ncls;
-    uint32_t *queue; // frames taken beyond the grid's first ones (zero before the launch), or null: none left
+    uint32_t *queue; // counters of the frames past the grid's first ones (zero before the launch), or null: none left
+    int32_t nq;      // counters in use
 };
 
 // The rows of one group: `held` their bits' slots in registers, or `tab`
@@ -202,7 +206,11 @@ __global__ __launch_bounds__(kMaxThreads) void k_lds(const LdsJob J, int32_t L, 
     }
 
     // ---- first frames ---------------------------------------------------------
-    const int32_t first_free = (int32_t)gridDim.x * F; // frames past the grid's first ones come from the counter
+    const int32_t dealt = (int32_t)gridDim.x * F, left = B - dealt; // frames past the first ones: from the counters
+    // thread 0: the next frame of a slot
+    auto draw = [&](int32_t &hc, uint32_t &dead) {
+        return J.queue ? dealt + take_frame(J.queue, left, J.nq, hc, dead) : B;
+    };
     int32_t fr[F], tt[F], ph[F];                       // ph: (tt - 1) modulo the test period
     V rc[CPT], rnx[CPT];                               // channel LLRs: own slots, next frame's own bits
 #pragma unroll
@@ -213,12 +221,12 @@ __global__ __launch_bounds__(kMaxThreads) void k_lds(const LdsJob J, int32_t L, 
     }
     if (tid == 0) {
         sh->red[0] = sh->red[1] = 0u;
+        int32_t hc = J.queue ? (int32_t)(blockIdx.x % (uint32_t)J.nq) : 0;
+        uint32_t dead = 0u;
 #pragma unroll
-        for (int q = 0; q < F; ++q) {
-            int64_t f = B;
-            if (J.queue && fr[q] < B) f = (int64_t)first_free + atomicAdd(J.queue, 1u);
-            sh->next[q] = f < B ? (int32_t)f : B;
-        }
+        for (int q = 0; q < F; ++q) sh->next[q] = draw(hc, dead);
+        sh->hc = hc;
+        sh->dead = dead;
     }
     const uint16_t *__restrict__ slot_of = J.t.slot_of; // of a bit
 #pragma unroll
@@ -363,13 +371,13 @@ __global__ __launch_bounds__(kMaxThreads) void k_lds(const LdsJob J, int32_t L, 
             for (int q = 0; q < F; ++q) more |= fr[q] < B;
             if (!more) break;
             if (tid == 0) {
+                int32_t hc = sh->hc;
+                uint32_t dead = sh->dead;
 #pragma unroll
                 for (int q = 0; q < F; ++q)
-                    if ((fin >> q) & 1u) {
-                        int64_t f = B;
-                        if (J.queue && fr[q] < B) f = (int64_t)first_free + atomicAdd(J.queue, 1u);
-                        sh->next[q] = f < B ? (int32_t)f : B;
-                    }
+                    if ((fin >> q) & 1u) sh->next[q] = draw(hc, dead);
+                sh->hc = hc;
+                sh->dead = dead;
             }
         }
         // ---- bit pass ---------------------------------------------------------------
@@ -442,8 +450,6 @@ __global__ __launch_bounds__(kMaxThreads) void k_lds(const LdsJob J, int32_t L, 
 
 using LdsFn = void (*)(const LdsJob, int32_t, int32_t);
 
-__global__ void k_zero_word(uint32_t *p) { *p = 0u; }
-
 // Bits per thread: 4, 8 or 16, the fewest that 1,024 threads need; 0 if more.
 int cpt_for(const ldpc_graph &g) { return g.n <= 4 * kMaxThreads ? 4 : g.n <= 8 * kMaxThreads ? 8 : g.n <= 16 * kMaxThreads ? 16 : 0; }
 
@@ -471,25 +477,36 @@ bool lds_fits(const ldpc_graph &g) {
 }
 
 int lds_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, uint32_t flags, const float *alpha,
-               const float *beta, uint8_t *bits, float *post, int32_t *iters, uint8_t *ok, void *ws, size_t ws_bytes,
+               const float *beta, uint8_t *bits, float *post, int32_t *iters, uint8_t *ok, void *ws,
                hipStream_t stream) {
     if (!lds_fits(g)) return LDPC_EUNSUPPORTED;
-    // the caller's workspace is sized for the streaming path, whatever kernel runs
-    if (ws == nullptr || ws_bytes < stream_workspace_bytes(g, B)) return LDPC_EWORKSPACE;
     const int cpt = cpt_for(g);
-    // Two frames per workgroup once every CU has one: the LDS moves a pair of
-    // frames for little more than one, but a frame alone finishes sooner.
-    const bool two = B > g.num_cu && g.dc_max <= 16 && cpt <= 8 && lds_bytes(g, 2) <= (size_t)g.lds_max;
-    const int F = two ? 2 : 1;
-    const LdsFn fn = kernel_for(F, cpt, g.dc_max, alpha != nullptr);
     const int waves = std::max(g.lds.row_groups, (g.lds.bit_groups + cpt - 1) / cpt);
     const int threads = 64 * std::min(waves, kMaxThreads / 64);
-    const size_t lds = lds_bytes(g, F);
-    int per_cu = 0;
-    if (hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)fn, threads, lds) != hipSuccess)
-        return LDPC_EHIP;
-    const int64_t room = (int64_t)std::max(per_cu, 1) * g.num_cu, groups = ((int64_t)B + F - 1) / F;
+    LdsFn fn = nullptr;
+    size_t lds = 0;
+    int64_t room = 0; // workgroups that the GPU holds
+    auto choose = [&](int F) {
+        fn = kernel_for(F, cpt, g.dc_max, alpha != nullptr);
+        lds = lds_bytes(g, F);
+        int per_cu = 0;
+        if (hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)fn, threads, lds) != hipSuccess)
+            return false;
+        room = (int64_t)std::max(per_cu, 1) * g.num_cu;
+        return true;
+    };
+    if (!choose(1)) return LDPC_EHIP;
+    // Two frames per workgroup once one per workgroup fills the GPU: the LDS
+    // moves a pair of frames for little more than one, but a frame alone
+    // finishes sooner (n = 500, irregular: 1,000 frames 0.099 ms with one and
+    // 0.116 with two, 2,000 frames 0.193 and 0.147).
+    int F = 1;
+    if (B > room && g.dc_max <= 16 && cpt <= 8 && lds_bytes(g, 2) <= (size_t)g.lds_max) {
+        F = 2;
+        if (!choose(2)) return LDPC_EHIP;
+    }
+    const int64_t groups = ((int64_t)B + F - 1) / F;
     const int grid = (int)std::min(room, groups);
     LdsJob J{};
     J.t = LdsTables{g.lds.rows, g.lds.bits, g.lds.row_group, g.lds.bit_group, g.lds.slot_of, g.lds.bit_of,
@@ -504,8 +521,9 @@ int lds_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, uint
     J.alpha = alpha;
     J.beta = beta;
     J.ncls = (int32_t)g.class_degrees.size();
-    J.queue = (int64_t)grid * F < B ? (uint32_t *)ws : nullptr;
-    if (J.queue) k_zero_word<<<1, 1, 0, stream>>>(J.queue);
+    J.queue = (int64_t)grid * F < B ? (uint32_t *)ws : nullptr; // (no smaller than the counters: any path's workspace)
+    J.nq = queues_for(std::max(B, 4 * grid)); // every workgroup draws at its start
+    if (J.queue) k_zero_words<<<(kQueueWords + 255) / 256, 256, 0, stream>>>(J.queue, kQueueWords);
     timed_launch(K_ONCHIP, fn, grid, threads, (uint32_t)lds, stream, J, L, test_period(flags));
     return hipGetLastError() == hipSuccess ? LDPC_OK : LDPC_EHIP;
 }

@@ -49,7 +49,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_onchip_multi(const JobTable jt,
 const KernelFn (*const kKernels[3])[kNumVariants] = {kKernelsW0, kKernelsW4, kKernelsW3};
 // Index of a register budget (waves per SIMD: 0, 4 or 3) in kKernels.
 inline int budget_index(int waves_per_simd) { return waves_per_simd == 4 ? 1 : waves_per_simd == 3 ? 2 : 0; }
-inline int tuned_budget(const ldpc_graph &g) { return g.tuning.set ? budget_index(g.tuning.waves_per_simd) : 0; }
+inline int tuned_budget(const ldpc_graph &g) { return g.tuned() ? budget_index(g.tuning.waves_per_simd) : 0; }
 
 // Threads: whole wavefronts, enough for RPT rows and CPT bits per thread.
 int threads_for(const ldpc_graph &g, const Variant &v) {
@@ -60,7 +60,7 @@ int threads_for(const ldpc_graph &g, const Variant &v) {
 }
 
 bool variant_ok(const ldpc_graph &g, int k) {
-    if (k < 0 || k >= kNumVariants) return false;
+    if (k < 0 || k >= kNumKernels) return false;
     const Variant &v = kVariants[k];
     const bool rows_ok = v.rx ? (g.dc_min == v.dc && g.dc_max == v.dc) : g.dc_max <= v.dc;
     // (a padded layout variant, cf & 4, takes columns of any degree up to its dv)
@@ -68,13 +68,13 @@ bool variant_ok(const ldpc_graph &g, int k) {
     // the layout's tables are for their own geometry, stride and thread count
     const bool cf_ok = v.cf == 0 || (g.cf.edge != nullptr && g.cf.rpt == v.rpt && g.cf.cpt == v.cpt &&
                                      g.cf.dvs == v.dv && g.cf.dvp == v.dvp && threads_for(g, v) == g.cf.nt);
-    const size_t state = v.cf != 0 ? cf_state_bytes(g) : state_bytes(g, v.f);
+    const size_t state = v.cf != 0 ? cf_state_bytes(g, v.f) : state_bytes(g, v.f);
     return rows_ok && cols_ok && cf_ok && threads_for(g, v) <= kMaxThreads && g.edge_tab != nullptr &&
            state + sizeof(Shared) + 1024 <= (size_t)g.lds_max;
 }
 
 size_t state_of(const ldpc_graph &g, int variant) {
-    return kVariants[variant].cf != 0 ? cf_state_bytes(g) : state_bytes(g, kVariants[variant].f);
+    return kVariants[variant].cf != 0 ? cf_state_bytes(g, kVariants[variant].f) : state_bytes(g, kVariants[variant].f);
 }
 size_t lds_of(const ldpc_graph &g, int variant) { return state_of(g, variant) + sizeof(Shared); }
 
@@ -87,10 +87,45 @@ static_assert(sizeof(kPickOrder) / sizeof(kPickOrder[0]) == kNumVariants, "every
 
 // The tuned variant if one is set and valid, else the first that fits.
 int pick(const ldpc_graph &g) {
-    if (g.tuning.set && variant_ok(g, g.tuning.variant)) return g.tuning.variant;
+    if (g.tuned() && variant_ok(g, g.tuning.variant)) return g.tuning.variant;
     for (int k : kPickOrder)
         if (variant_ok(g, k)) return k;
     return -1;
+}
+
+// Resident workgroups of a kernel on the whole GPU (at least one per CU); -1 on failure.
+int64_t room_of(const void *fn, int threads, size_t lds, int num_cu) {
+    int per_cu = 0;
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess)
+        return -1;
+    return (int64_t)std::max(per_cu, 1) * num_cu;
+}
+
+// Layout variants whose two-slot kernel takes more than 128 registers, so that
+// at most three of its waves share a SIMD: their one-slot form is the faster
+// one at every batch size (n = 1152, rows of 9, 20,000 frames: 0.406 ms with
+// two slots, 0.286 with one; rows of 12: 0.459 and 0.327).
+constexpr bool one_slot_always(int v) {
+    return v == 23 || v == 27 || v == 29 || v == 31 || v == 33 || v == 37 || v == 39 || v == 41;
+}
+
+// The kernel (index into kVariants) that decodes B frames: the picked variant,
+// or, without a tuning record, its one-slot form, whose rounds are about half
+// as long, while no more than four frames fall to each resident workgroup of
+// it ((3,6) n = 1024, B = 1,000: 0.069 ms with two slots and 0.045 with one;
+// 4,000: 0.097 and 0.092; 20,000: 0.233 and 0.253).
+int kernel_of(const ldpc_graph &g, int64_t B, bool learned) {
+    const int v = pick(g), o = v >= 0 ? one_slot(v) : -1;
+    if (o < 0 || g.tuned() || !variant_ok(g, o)) return v;
+    if (one_slot_always(v)) return o;
+    const int64_t room = room_of((const void *)kKernelsOne[learned ? 1 : 0][o - kNumVariants],
+                                 threads_for(g, kVariants[o]), lds_of(g, o), g.num_cu);
+    return B <= 4 * room ? o : v;
+}
+KernelFn kernel_fn(const ldpc_graph &g, int v, bool learned) {
+    return v >= kNumVariants ? kKernelsOne[learned ? 1 : 0][v - kNumVariants]
+                             : kKernels[tuned_budget(g)][learned ? 1 : 0][v];
 }
 
 Job make_job(const ldpc_graph &g, int variant, const float *llr, int32_t B, uint8_t *bits, float *post,
@@ -108,7 +143,7 @@ Job make_job(const ldpc_graph &g, int variant, const float *llr, int32_t B, uint
     J.cf_bitpos = g.cf.bitpos;
     J.cf_slot_bit = g.cf.slot_bit;
     J.cf_row_class = g.cf.row_class;
-    J.cf_eta_off = cf_eta_offset(g);
+    J.cf_eta_off = cf_eta_offset(g, kVariants[variant].f);
     J.cf_npos = g.cf.npos;
     J.llr = llr;
     J.B = B;
@@ -120,27 +155,31 @@ Job make_job(const ldpc_graph &g, int variant, const float *llr, int32_t B, uint
     J.beta = beta;
     J.ncls = (int32_t)g.class_degrees.size();
     J.variant = variant;
+    J.dealt = 0;
     J.queue = queue;
     J.nq = queues_for(B);
     return J;
 }
 
-__global__ void k_zero_words(uint32_t *p, int32_t count) {
-    const int32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < count) p[k] = 0u;
+// A launch of `grid` workgroups for one job with a one-slot kernel: the first
+// frames are dealt, and where those are all, no counter is needed (nor the
+// launch that clears it).  Every workgroup draws its second frame at the start,
+// so the counters are spread for those as well.
+void deal(Job &J, int grid) {
+    if (J.variant < kNumVariants) return;
+    J.dealt = std::min(grid, J.B);
+    if (J.dealt == J.B) J.queue = nullptr;
+    else J.nq = queues_for(std::max(J.B - J.dealt, 4 * grid));
 }
 
 // Grid of a persistent launch: every CU filled to its occupancy, but no more
-// workgroups than there are groups of 2 F frames.
+// workgroups than there are groups of `per_wg` frames.
 int launch_grid(const void *fn, int threads, size_t lds, int num_cu, int64_t frames, int cap_per_cu, int *grid,
-                int F = 2) {
-    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return LDPC_EHIP;
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess) return LDPC_EHIP;
-    if (cap_per_cu > 0 && per_cu > cap_per_cu) per_cu = cap_per_cu;
-    per_cu = per_cu < 1 ? 1 : per_cu;
-    const int64_t groups = (frames + 2 * F - 1) / (2 * F);
-    const int64_t want = (int64_t)num_cu * per_cu;
+                int per_wg) {
+    int64_t want = room_of(fn, threads, lds, num_cu);
+    if (want < 0) return LDPC_EHIP;
+    if (cap_per_cu > 0) want = std::min(want, (int64_t)num_cu * cap_per_cu);
+    const int64_t groups = (frames + per_wg - 1) / per_wg;
     *grid = (int)(want < groups ? want : groups);
     if (*grid < 1) *grid = 1;
     return LDPC_OK;
@@ -225,6 +264,11 @@ bool onchip_cf_geometry(const ldpc_graph &g, const std::vector<int32_t> &col_deg
 
 bool onchip_fits(const ldpc_graph &g) { return g.edge_tab != nullptr && pick(g) >= 0; }
 
+bool onchip_masks_rows(const ldpc_graph &g) {
+    const int v = pick(g);
+    return v >= 0 && !kVariants[v].rx;
+}
+
 bool onchip_variant_fits(const ldpc_graph &g, int variant) { return variant_ok(g, variant); }
 
 int onchip_num_variants() { return kNumVariants; }
@@ -259,20 +303,20 @@ int onchip_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, u
     (void)T;
     if (!onchip_fits(g)) return LDPC_EUNSUPPORTED;
     if (ws == nullptr || ws_bytes < onchip_workspace_bytes(g, B)) return LDPC_EWORKSPACE;
-    const int v = pick(g);
-    const KernelFn fn = kKernels[tuned_budget(g)][alpha != nullptr ? 1 : 0][v];
-    const int threads = threads_for(g, kVariants[v]);
+    const int v = kernel_of(g, B, alpha != nullptr);
+    const KernelFn fn = kernel_fn(g, v, alpha != nullptr);
+    const int threads = threads_for(g, kVariants[v]), per_wg = v >= kNumVariants ? 1 : 2 * kVariants[v].f;
     const size_t lds = lds_of(g, v);
     int grid = 0;
-    int st = launch_grid((const void *)fn, threads, lds, g.num_cu, B, g.tuning.set ? g.tuning.wg_per_cu : 0, &grid,
-                         kVariants[v].f);
+    int st = launch_grid((const void *)fn, threads, lds, g.num_cu, B, g.tuned() ? g.tuning.wg_per_cu : 0, &grid,
+                         per_wg);
     if (st) return st;
-    uint32_t *queue = (uint32_t *)ws;
     const int32_t early = test_period(flags);
     JobTable jt{};
     jt.njobs = 1;
-    jt.job[0] = make_job(g, v, llr, B, bits, post, iters, ok, alpha, beta, queue);
-    k_zero_words<<<(kQueueWords + 255) / 256, 256, 0, stream>>>(queue, kQueueWords);
+    Job &J = jt.job[0] = make_job(g, v, llr, B, bits, post, iters, ok, alpha, beta, (uint32_t *)ws);
+    deal(J, grid);
+    if (J.queue) k_zero_words<<<(kQueueWords + 255) / 256, 256, 0, stream>>>(J.queue, kQueueWords);
     timed_launch(K_ONCHIP, fn, grid, threads, lds, stream, jt, L, early);
     return hipGetLastError() == hipSuccess ? LDPC_OK : LDPC_EHIP;
 }
@@ -318,7 +362,7 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
         const ldpc_graph &g = *jb.g;
         if (!onchip_fits(g)) return LDPC_EUNSUPPORTED;
         if (jb.B == 0) continue;
-        const int v_own = pick(g);
+        const int v_own = kernel_of(g, jb.B, false);
         int v = v_own;
         if (!shared_launch_ok(v)) // another variant that fits keeps the job eligible for the shared launch
             for (int c : kPickOrder)
@@ -326,23 +370,20 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
                     v = c;
                     break;
                 }
-        const KernelFn fn = kKernels[tuned_budget(g)][0][v_own];
+        const KernelFn fn = kernel_fn(g, v_own, false);
         const int t_own = threads_for(g, kVariants[v_own]);
         const size_t l_own = lds_of(g, v_own);
         bool alone = !shared_launch_ok(v);
         if (!alone) {
-            int per_cu = 0;
-            if (hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)l_own) !=
-                    hipSuccess ||
-                hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)fn, t_own, l_own) != hipSuccess)
-                return LDPC_EHIP;
-            const int64_t in_flight = (int64_t)(per_cu < 1 ? 1 : per_cu) * g.num_cu * kVariants[v_own].f;
+            const int64_t room = room_of((const void *)fn, t_own, l_own, g.num_cu);
+            if (room < 0) return LDPC_EHIP;
+            const int64_t in_flight = room * kVariants[v_own].f;
             alone = (int64_t)jb.B >= kOwnLaunchRounds * in_flight;
         }
         if (alone) {
             own.push_back(Own{make_job(g, v_own, jb.llr_dev, jb.B, jb.bits_dev, jb.post_dev, jb.iters_dev, jb.ok_dev,
                                        nullptr, nullptr, queues + (size_t)k * kQueueWords),
-                              fn, t_own, l_own, g.num_cu, g.tuning.set ? g.tuning.wg_per_cu : 0});
+                              fn, t_own, l_own, g.num_cu, g.tuned() ? g.tuning.wg_per_cu : 0});
             continue;
         }
         const int t = threads_for(g, kVariants[v]);
@@ -387,13 +428,16 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
         }
         int grid = 0;
         const int st = launch_grid((const void *)own[a].fn, t, l, own[a].num_cu, fr, own[a].wg_per_cu, &grid,
-                                   kVariants[own[a].J.variant].f);
+                                   ot.njobs == 1 && own[a].J.variant >= kNumVariants
+                                       ? 1
+                                       : 2 * kVariants[own[a].J.variant].f);
         if (st) return st;
+        if (ot.njobs == 1) deal(ot.job[0], grid);
         launches.push_back(Launch{own[a].fn, grid, t, l, ot});
     }
     if (frames > 0) {
         int grid = 0;
-        const int st = launch_grid((const void *)k_onchip_multi, threads, lds, num_cu, frames, 0, &grid);
+        const int st = launch_grid((const void *)k_onchip_multi, threads, lds, num_cu, frames, 0, &grid, 4);
         if (st) return st;
         launches.push_back(Launch{k_onchip_multi, grid, threads, lds, jt});
     }

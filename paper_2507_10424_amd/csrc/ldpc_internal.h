@@ -97,7 +97,7 @@ struct ldpc_graph {
     struct {
         bool set = false;
         int path = 0;         // 1 on-chip, 2 streaming
-        bool lds = false;     // path 2 from the autotuner, but the LDS-resident decoder was faster
+        bool idle = false;    // from the autotuner: decoding without a record was faster than this one
         int variant = -1;     // on-chip kernel variant
         int wg_per_cu = 0;    // on-chip workgroups per CU (0: occupancy limit)
         int waves_per_simd = 0; // on-chip register budget: 0 compiler's, 4 / 3 at least 4 / 3 waves per SIMD
@@ -105,6 +105,7 @@ struct ldpc_graph {
         int stream_nt = -1;   // non-temporal message accesses: 1 yes, 0 no, -1 by size
         int stream_chunk = -1; // tiles per chunk of the streaming path: 0 all, -1 by size
     } tuning;
+    bool tuned() const { return tuning.set && !tuning.idle; }
 };
 
 #define LDPC_HIP_TRY(expr)                                   \
@@ -127,6 +128,9 @@ int32_t stream_chunk_tiles(const ldpc_graph &g, int32_t B, int32_t chunk);
 
 // On-chip (LDS-resident) decoder: whether the graph fits, workspace, launch.
 bool onchip_fits(const ldpc_graph &g);
+// Whether the on-chip path would decode the graph with masked rows, where the
+// LDS-resident decoder is faster.
+bool onchip_masks_rows(const ldpc_graph &g);
 bool onchip_variant_fits(const ldpc_graph &g, int variant);
 int onchip_num_variants();
 // Whether the kernel of (variant, register budget) needs no scratch (no spills).
@@ -167,14 +171,14 @@ bool onchip_cf_geometry(const ldpc_graph &g, const std::vector<int32_t> &col_deg
 
 // LDS-resident decoder for other codes whose state fits one CU: its tables
 // (false if the graph is out of its range), whether it takes the graph, launch
-// (the workspace is the streaming path's).
+// (of the workspace, whichever path's, it uses the first 2,176 bytes).
 constexpr int kLdsMaxThreads = 1024; // of a workgroup
 constexpr int kLdsMaxDegree = 32;    // of a row
 bool lds_tables(const std::vector<int32_t> &rowptr, const std::vector<int32_t> &col,
                 const std::vector<int32_t> &row_class, int32_t m, int32_t n, LdsHostTables *out);
 bool lds_fits(const ldpc_graph &g);
 int lds_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, uint32_t flags, const float *alpha,
-               const float *beta, uint8_t *bits, float *post, int32_t *iters, uint8_t *ok, void *ws, size_t ws_bytes,
+               const float *beta, uint8_t *bits, float *post, int32_t *iters, uint8_t *ok, void *ws,
                hipStream_t stream);
 
 // Order of the rows for the streaming check kernel (roworder.hip): a

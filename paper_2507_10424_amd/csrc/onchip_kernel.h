@@ -49,6 +49,7 @@
 
 #include <algorithm>
 
+#include "frame_queue.h"
 #include "ldpc_internal.h"
 #include "minsum_row.h"
 
@@ -75,72 +76,19 @@ struct Shared {          // small shared words, placed after s and eta
     uint32_t dead;       // thread 0: counters found exhausted
 };
 
-// Frame counters.  One counter handing out every frame number would be a
-// single address that every refill of every workgroup increments atomically;
-// when frames stop after a few iterations, those atomics (one per frame, all
-// serialised at one address) bound the decoder.  So each job has kQueues
-// counters, each in a 128-byte line of its own: counter c hands out frames
-// c, c + kQueues, c + 2 kQueues, ...  A workgroup draws from one counter and
-// moves to another live one when it finds its counter exhausted, so all
-// frames are taken before any workgroup runs out.
-constexpr int kQueues = 16;
-constexpr int kQueueStride = 32; // 32-bit words between counters
-// the counters, then one word (in a line of its own) with a bit for every
-// counter some workgroup has found exhausted
-constexpr int kQueueWords = (kQueues + 1) * kQueueStride;
-
-// Frame number of the k-th value taken from counter c of nq.
-__device__ __forceinline__ int64_t frame_of(uint32_t k, int32_t c, int32_t nq) { return (int64_t)k * nq + c; }
-
-// Counters a batch of B frames uses: one per 1,024 frames, at most kQueues
-// (a small batch needs no spreading, and every counter a workgroup finds
-// exhausted costs it one atomic round trip at the end).
-inline int32_t queues_for(int32_t B) {
-    const int32_t q = B / 1024;
-    return q < 1 ? 1 : (q > kQueues ? kQueues : q);
-}
-
-// The next live counter after c, or c when none is left.
-__device__ __forceinline__ int32_t next_live(int32_t c, uint32_t dead, int32_t nq) {
-    for (int d = 1; d < nq; ++d) {
-        const int32_t x = (c + d) % nq;
-        if (!((dead >> x) & 1u)) return x;
-    }
-    return c;
-}
-
-// Records that counter c is exhausted and learns which others are, in one
-// atomic on the shared exhausted-counter word.
-__device__ __forceinline__ uint32_t mark_dead(uint32_t *queue, int32_t c, uint32_t dead) {
-    return dead | (1u << c) | atomicOr(queue + kQueues * kQueueStride, 1u << c);
-}
-
-// One thread: a frame number below B from the live counters (blocking), or B
-// when all are exhausted.  `hc` is the counter to try first (live unless all
-// are dead); each failed attempt marks at least one more counter dead, so
-// the loop ends after at most nq attempts.
-__device__ __forceinline__ int32_t take_frame(uint32_t *queue, int32_t B, int32_t nq, int32_t &hc, uint32_t &dead) {
-    const uint32_t all = (1u << nq) - 1u;
-    while ((dead & all) != all) {
-        if ((dead >> hc) & 1u) hc = next_live(hc, dead, nq); // some counter is live
-        const int64_t f = frame_of(atomicAdd(queue + hc * kQueueStride, 1u), hc, nq);
-        if (f < B) return (int32_t)f;
-        dead = mark_dead(queue, hc, dead);
-    }
-    return B;
-}
-
 // s[n] and eta[E + 1] (one padding slot), F floats per entry, then Shared
 inline size_t state_bytes(const ldpc_graph &g, int F) {
     return align_up(sizeof(float) * (size_t)F * ((size_t)g.n + (size_t)g.E + 1), 16);
 }
 
 
-// The bank-conflict-free layout (two frame slots, 8-byte entries): s[n], then
-// the messages from a 256-byte boundary (so that a position's bank class is
-// the position modulo 32), cf.npos entries.
-inline uint32_t cf_eta_offset(const ldpc_graph &g) { return (uint32_t)align_up(8 * (size_t)g.n, 256); }
-inline size_t cf_state_bytes(const ldpc_graph &g) { return align_up(cf_eta_offset(g) + 8 * (size_t)g.cf.npos, 16); }
+// The bank-conflict-free layout (one or two frame slots): s[n], then the
+// messages from a 256-byte boundary (so that a position's bank class is the
+// position modulo 32), cf.npos entries.
+inline uint32_t cf_eta_offset(const ldpc_graph &g, int F) { return (uint32_t)align_up(4 * (size_t)F * g.n, 256); }
+inline size_t cf_state_bytes(const ldpc_graph &g, int F) {
+    return align_up(cf_eta_offset(g, F) + 4 * (size_t)F * (size_t)g.cf.npos, 16);
+}
 
 template <class V> __device__ __forceinline__ V lds_ld(const unsigned char *base, uint32_t off) {
     return *reinterpret_cast<const V *>(base + off);
@@ -184,8 +132,12 @@ struct Job {
     const float *alpha, *beta; // learned weights (T x ncls) or null
     int32_t ncls;
     int32_t variant;  // index into kVariants
-    uint32_t *queue;  // kQueues frame counters (kQueueStride words apart), zero before the launch
-    int32_t nq;       // counters in use (queues_for(B))
+    // One-slot kernels: frame k below `dealt` goes to workgroup k, the others are
+    // taken from the counters.
+    int32_t dealt;
+    uint32_t *queue;  // kQueues frame counters (kQueueStride words apart), zero before the launch;
+                      // null if every frame is dealt
+    int32_t nq;       // counters in use (queues_for)
     // bank-conflict-free layout (CF variants): tables of the graph, the LDS
     // byte offset of the messages and their number of positions
     const uint32_t *cf_edge;
@@ -221,7 +173,7 @@ __device__ __forceinline__ void run_onchip(const Job &J, int32_t L, int32_t earl
     constexpr bool kLay = (CF & 3) != 0;     // the layout's tables
     constexpr bool kPrevLds = (CF & 3) == 1; // previous messages read from LDS
     constexpr bool kPad = (CF & 4) != 0;     // columns padded with zero messages
-    static_assert(!kLay || (RX && CX && F == 2), "layout: rows of one degree, padded columns, 8-byte entries");
+    static_assert(!kLay || (RX && CX && F <= 2), "layout: rows of one degree, padded columns, entries of 4 or 8 bytes");
     typedef typename Vec<F>::type V;
     constexpr uint32_t kEnt = sizeof(V); // bytes of one LDS entry (F floats)
     // read all s (messages) of the check (bit) pass up front when that takes
@@ -314,25 +266,42 @@ __device__ __forceinline__ void run_onchip(const Job &J, int32_t L, int32_t earl
     }
 
     // ---- slots --------------------------------------------------------------
+    // One slot: the first frames are dealt, and the counters (null if that is
+    // all) hand out the others.  (Elsewhere the five registers that this takes
+    // would cost the two-slot kernels a wave per SIMD.)
+    constexpr bool kDeal = kLay && F == 1;
+    const int32_t dealt = kDeal ? J.dealt : 0, left = B - dealt;
     if (tid == 0) {
-        // 2 F consecutive values of the home counter with one atomic; any
-        // that fall past B come from the other counters
+        // 2 F consecutive values of the home counter with one atomic (F, where
+        // the first F are dealt); any that fall past the end come from the
+        // other counters
         int32_t hc = (int32_t)(blockIdx.x % (uint32_t)nq);
         uint32_t dead = 0u;
-        const uint32_t k0 = atomicAdd(queue + hc * kQueueStride, 2u * F);
-        const int32_t home = hc;
+        const int first = kDeal && dealt > 0 ? F : 0;
         int32_t fs[2 * F];
+        if constexpr (kDeal) {
 #pragma unroll
-        for (int i = 0; i < 2 * F; ++i) {
-            const int64_t f = frame_of(k0 + (uint32_t)i, home, nq);
-            if (f < B) {
-                fs[i] = (int32_t)f;
-            } else {
-                if (!((dead >> home) & 1u)) {
-                    dead = mark_dead(queue, home, dead);
-                    hc = next_live(home, dead, nq);
+            for (int i = 0; i < F; ++i) {
+                fs[i] = (int32_t)blockIdx.x * F + i; // (overwritten unless dealt)
+                fs[F + i] = B;
+            }
+        }
+        if (!kDeal || queue) {
+            const uint32_t k0 = atomicAdd(queue + hc * kQueueStride, 2u * F - (uint32_t)first);
+            const int32_t home = hc;
+#pragma unroll
+            for (int i = 0; i < 2 * F; ++i) {
+                if (kDeal && i < first) continue;
+                const int64_t f = frame_of(k0 + (uint32_t)(i - first), home, nq);
+                if (f < left) {
+                    fs[i] = dealt + (int32_t)f;
+                } else {
+                    if (!((dead >> home) & 1u)) {
+                        dead = mark_dead(queue, home, dead);
+                        hc = next_live(home, dead, nq);
+                    }
+                    fs[i] = dealt + take_frame(queue, left, nq, hc, dead);
                 }
-                fs[i] = take_frame(queue, B, nq, hc, dead);
             }
         }
 #pragma unroll
@@ -579,11 +548,15 @@ __device__ __forceinline__ void run_onchip(const Job &J, int32_t L, int32_t earl
             }
             const int32_t nf = __builtin_amdgcn_readfirstlane(sh->next[q][gen[q] & 1]);
             if (tid == 0) { // the slot's frame after next
-                int32_t hc = sh->hc;
-                uint32_t dead = sh->dead;
-                sh->next[q][(gen[q] + 1) & 1] = take_frame(queue, B, nq, hc, dead);
-                sh->hc = hc;
-                sh->dead = dead;
+                int32_t nn = B;
+                if (!kDeal || queue) {
+                    int32_t hc = sh->hc;
+                    uint32_t dead = sh->dead;
+                    nn = dealt + take_frame(queue, left, nq, hc, dead);
+                    sh->hc = hc;
+                    sh->dead = dead;
+                }
+                sh->next[q][(gen[q] + 1) & 1] = nn;
             }
             fr[q] = nf;
             gen[q] += 1;
@@ -756,8 +729,35 @@ constexpr Variant kVariants[] = {
     {9, true, 6, true, 2, 6, 2, 5, 0x633222u},    {9, true, 6, true, 2, 6, 2, 6, 0x633222u},
     {12, true, 6, true, 1, 4, 2, 5, 0x6332u},     {12, true, 6, true, 1, 4, 2, 6, 0x6332u},
     {16, true, 4, true, 1, 6, 2, 5, 0x433222u},   {16, true, 4, true, 1, 6, 2, 6, 0x433222u},
+    // One-slot forms of the layout variants with their messages in registers
+    // (15, 33 to 41 and 23 to 31), for batches that leave the GPU idle
+    // otherwise; not choices of the tuning record.
+    {6, true, 3, true, 2, 4, 1, 2},               {6, true, 6, true, 2, 4, 1, 6, 0x6332u},
+    {6, true, 6, true, 1, 2, 1, 6, 0x63u},        {9, true, 6, true, 2, 6, 1, 6, 0x633222u},
+    {12, true, 6, true, 1, 4, 1, 6, 0x6332u},     {16, true, 4, true, 1, 6, 1, 6, 0x433222u},
+    {6, true, 6, true, 2, 4, 1, 6},               {6, true, 6, true, 1, 2, 1, 6},
+    {9, true, 6, true, 2, 6, 1, 6},               {12, true, 6, true, 1, 4, 1, 6},
+    {16, true, 4, true, 1, 6, 1, 6},
 };
-constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
+constexpr int kNumKernels = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
+constexpr int kNumVariants = 42; // of the tuning record
+// The one-slot form of a variant, -1 if it has none.
+constexpr int one_slot(int v) {
+    switch (v) {
+    case 15: return 42;
+    case 33: return 43;
+    case 35: return 44;
+    case 37: return 45;
+    case 39: return 46;
+    case 41: return 47;
+    case 23: return 48;
+    case 25: return 49;
+    case 27: return 50;
+    case 29: return 51;
+    case 31: return 52;
+    default: return -1;
+    }
+}
 
 template <int V, bool NMS>
 __device__ __forceinline__ void run_v(const Job &J, int32_t L, int32_t early, unsigned char *lds) {
@@ -803,10 +803,11 @@ using KernelFn = void (*)(const JobTable, int32_t, int32_t);
      &k_onchip<35, W, N>, &k_onchip<36, W, N>, &k_onchip<37, W, N>, &k_onchip<38, W, N>, &k_onchip<39, W, N>,         \
      &k_onchip<40, W, N>, &k_onchip<41, W, N>}
 // The kernels of each register budget (waves per SIMD 0, 4, 3), one source
-// file each: [learned][variant].
+// file each: [learned][variant]; the one-slot forms with the compiler's.
 extern const KernelFn kKernelsW0[2][kNumVariants];
 extern const KernelFn kKernelsW4[2][kNumVariants];
 extern const KernelFn kKernelsW3[2][kNumVariants];
+extern const KernelFn kKernelsOne[2][kNumKernels - kNumVariants];
 
 } // namespace onchip
 } // namespace ldpc

@@ -1,0 +1,61 @@
+"""Batches around the sizes where the on-chip path changes its launch: one-slot
+kernels for few frames, first frames dealt to the workgroups, further ones from
+the counters.  Every frame against the streaming path, some against the oracle."""
+import numpy as np
+import pytest
+
+from paper_2507_10424_amd import workloads as wl
+from parity import assert_parity, note, oracle_decode
+
+pytestmark = pytest.mark.gpu
+
+
+def _codes():
+    fam = wl.qc_multi_code_family(seed=7)
+    out = {f"qc{k}": (c["H"], c["rate"]) for k, c in enumerate(fam)}
+    out["regular96"] = (wl.regular_ldpc(96, 48, 3, 6, seed=1), 0.5)
+    out["regular1024"] = (wl.regular_ldpc(1024, 512, 3, 6, seed=2), 0.5)
+    # masked columns (no layout), and layouts padded without a degree profile
+    out["masked_columns"] = (wl.regular_ldpc(600, 300, 4, 8, seed=3), 0.5)
+    out["columns_8"] = (wl.regular_ldpc(240, 180, 6, 8, seed=3), 0.3)
+    for k, (dv, dc) in enumerate([(2, 6), (4, 9), (5, 12), (3, 16)]):
+        out[f"padded_{dv}_{dc}"] = (wl.regular_ldpc(dc * 36, dv * 36, dv, dc, seed=5 + k), 1 - dv / dc)
+    return out
+
+
+CODES = _codes()
+
+
+@pytest.mark.parametrize("name", sorted(CODES))
+def test_small_batches(name):
+    import torch
+    from paper_2507_10424_amd import ldpc
+    dev = torch.device("cuda:0")
+    H, rate = CODES[name]
+    g = ldpc.build_graph(torch.from_numpy(np.ascontiguousarray(H)).to(dev))
+    C, T = len(g.check_degrees), 12
+    rng = np.random.default_rng(3)
+    alpha = rng.uniform(0.6, 1.1, size=(T, C)).astype(np.float32)
+    beta = rng.uniform(0.0, 0.3, size=(T, C)).astype(np.float32)
+    al, be = torch.from_numpy(alpha).to(dev), torch.from_numpy(beta).to(dev)
+    cus = torch.cuda.get_device_properties(dev).multi_processor_count
+    for B in (1, 2, 3, cus + 1, 4 * cus, 4 * cus + 1, 9 * cus + 5):
+        note(f"[small] {name} B={B}")
+        llr = wl.bpsk_awgn_llr(None, 1.5 + 5.5 * max(0.0, rate - 0.5), rate, seed=B, n=g.n, batch=B)
+        x = torch.from_numpy(llr).to(dev)
+        some = slice(max(0, B - 6), B)
+        for learned in (False, True):
+            def run(flags, out=None):
+                if learned:
+                    return ldpc.nms_decode(g, x, T, al, be, flags=flags, out=out)
+                return ldpc.minsum_decode(g, x, 20, flags=flags, out=out)
+            out = ldpc._outputs(B, g.n, dev, True)
+            for t, v in zip(out, (7, float("nan"), -7, 9)):
+                t.fill_(v)
+            run(0, out)
+            ref = run(ldpc.LDPC_FORCE_STREAM)
+            torch.cuda.synchronize()
+            for a, b in zip(out, ref):
+                assert torch.equal(a, b), (name, B, learned)
+            want = oracle_decode(H, llr[some], T, 0, alpha, beta) if learned else oracle_decode(H, llr[some], 20)
+            assert_parity(tuple(t.cpu().numpy()[some] for t in out), want, f"{name} B={B} learned={learned}")
