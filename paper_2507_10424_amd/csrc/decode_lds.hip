@@ -22,8 +22,8 @@
 // frame-iteration through the Infinity Cache instead, two launches each, and
 // runs a tile of 64 frames until its last one stops.  Whole calls, streaming
 // before and this kernel now: n = 8176, rows of 32, 1,500 frames, 2.78 ms and
-// 0.319 ms; n = 4000, rows of 2 to 14, 777 frames, 1.57 and 0.219 ms; the
-// (3,6) code of n = 4096, 333 frames, 20 iterations, 0.340 and 0.074 ms.
+// 0.276 ms; n = 4000, rows of 2 to 14, 777 frames, 1.57 and 0.209 ms; the
+// (3,6) code of n = 4096, 333 frames, 20 iterations, 0.340 and 0.071 ms.
 //
 // Row arithmetic, order of the sums, tests and outputs are those of the
 // on-chip kernel (onchip_kernel.h); padding edges read a posterior of
@@ -161,8 +161,9 @@ __device__ __forceinline__ void check_group(int32_t deg, unsigned char *lds, con
 #undef LDPC_ROWS
 }
 
-// MAXD: largest row degree (8, 16 or 32).  CPT: bits per thread at most.
-template <int F, int CPT, int MAXD, bool NMS>
+// MAXD: largest row degree (8, 16 or 32).  CPT: bits per thread at most.  ALL:
+// the registers hold the neighbour tables of all groups.
+template <int F, int CPT, int MAXD, bool NMS, bool ALL>
 __global__ __launch_bounds__(kMaxThreads) void k_lds(const LdsJob J, int32_t L, int32_t early) {
     typedef typename Vec<F>::type V;
     constexpr uint32_t kEnt = sizeof(V);
@@ -303,7 +304,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_lds(const LdsJob J, int32_t L, 
                                           usyn);
             }
         }
-        for (int32_t g = w + kRowGroups * nw; g < J.t.row_groups; g += nw) {
+        for (int32_t g = w + kRowGroups * nw; !ALL && g < J.t.row_groups; g += nw) {
             const LdsGroup G = J.t.row_group[g];
             if constexpr (NMS) weights(J.t.row_class[g * 64 + lr]);
             check_group<MAXD, F, NMS>(G.degree, lds, nullptr, rowtab + G.table + lr,
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_lds(const LdsJob J, int32_t L, 
 #pragma unroll
                     for (int k = 1; k < kBitWords; ++k)
                         if (2 * k < d) acc = acc + pa[k] + pb[k];
-                    if (d > 2 * kBitWords) {
+                    if (!ALL && d > 2 * kBitWords) {
                         const uint32_t *tab = bittab + J.t.bit_group[g].table + lr;
                         for (int32_t k = kBitWords; 2 * k < d; ++k) {
                             const uint32_t h = tab[64 * k];
@@ -461,11 +462,12 @@ size_t lds_bytes(const ldpc_graph &g, int F) {
 // per thread.  Two frames only with rows of at most 16 (a row of 32 would
 // take 128 registers for its posteriors and messages alone) and at most 8
 // bits per thread (more do not fit two frames in the LDS anyway).
-LdsFn kernel_for(int F, int cpt, int maxd, bool nms) {
+template <bool ALL> LdsFn kernel_for(int F, int cpt, int maxd, bool nms) {
 #define LDPC_K(F_, C_, D_)                                                                                           \
-    if (F == F_ && cpt == C_ && maxd <= D_) return nms ? &k_lds<F_, C_, D_, true> : &k_lds<F_, C_, D_, false>;
+    if (F == F_ && cpt == C_ && maxd <= D_) return nms ? &k_lds<F_, C_, D_, true, ALL> : &k_lds<F_, C_, D_, false, ALL>;
     LDPC_K(1, 4, 8) LDPC_K(1, 4, 16) LDPC_K(1, 4, 32) LDPC_K(1, 8, 8) LDPC_K(1, 8, 16) LDPC_K(1, 8, 32)
-    LDPC_K(1, 16, 32) LDPC_K(2, 4, 8) LDPC_K(2, 4, 16) LDPC_K(2, 8, 8) LDPC_K(2, 8, 16)
+    LDPC_K(2, 4, 8) LDPC_K(2, 8, 8)
+    if constexpr (!ALL) { LDPC_K(1, 16, 32) LDPC_K(2, 4, 16) LDPC_K(2, 8, 16) }
 #undef LDPC_K
     return nullptr;
 }
@@ -481,13 +483,19 @@ int lds_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, uint
                hipStream_t stream) {
     if (!lds_fits(g)) return LDPC_EUNSUPPORTED;
     const int cpt = cpt_for(g);
-    const int waves = std::max(g.lds.row_groups, (g.lds.bit_groups + cpt - 1) / cpt);
-    const int threads = 64 * std::min(waves, kMaxThreads / 64);
+    const int waves = std::min(std::max(g.lds.row_groups, (g.lds.bit_groups + cpt - 1) / cpt), kMaxThreads / 64);
+    const int threads = 64 * waves;
+    // What the registers hold: two groups of rows per wavefront (one of rows
+    // above 16), and 8 messages of a bit (4 where a thread has 8 bits).
+    const bool all = cpt <= 8 && g.lds.row_groups <= (g.dc_max > 16 ? 1 : 2) * waves && g.dv_max <= (cpt <= 4 ? 8 : 4);
     LdsFn fn = nullptr;
     size_t lds = 0;
     int64_t room = 0; // workgroups that the GPU holds
     auto choose = [&](int F) {
-        fn = kernel_for(F, cpt, g.dc_max, alpha != nullptr);
+        // (two frames with rows of up to 16 spill more in the form for all groups:
+        // n = 4000, 0.209 ms without it and 0.217 with it)
+        fn = all && !(F == 2 && g.dc_max > 8) ? kernel_for<true>(F, cpt, g.dc_max, alpha != nullptr)
+                                              : kernel_for<false>(F, cpt, g.dc_max, alpha != nullptr);
         lds = lds_bytes(g, F);
         int per_cu = 0;
         if (hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||

@@ -25,10 +25,45 @@ namespace ldpc {
 
 constexpr int kTrainMaxClasses = 8;
 
-__device__ __forceinline__ float softplusf(float z) { return fmaxf(z, 0.0f) + log1pf(expf(-fabsf(z))); }
+// exp(-|z|) as 2^-x, x = |z| log2(e) to twice the precision: the hardware's
+// 2^x of the rounded x, times one plus the exponent's remainder.  (The general
+// expf and log1pf take about 150 instructions for a softplus, four times a
+// posterior's share of everything else; these take 25 and a sigmoid 17.  On
+// 3 million values from -110 to 110 the largest relative errors are 4.6 and
+// 3.8 units of 2^-24, of the library functions 4.8 and 4.3.)  NaN stays NaN.
+__device__ __forceinline__ float exp_minus_abs(float z) {
+    constexpr double kLog2e = 1.4426950408889634;
+    constexpr float hi = (float)kLog2e, lo = (float)(kLog2e - (double)hi);
+    float a = fabsf(z);
+    a = a > 104.0f ? 104.0f : a; // 2^-150 and below: 0 in binary32
+    const float x = a * hi;
+    const float rest = fmaf(a, lo, fmaf(a, hi, -x));
+    const float e = __builtin_amdgcn_exp2f(-x);
+    return fmaf(e, -0.6931471805599453f * rest, e);
+}
+// num / d to about one unit in the last place: the hardware's reciprocal and
+// one correction of the quotient (d between 1 and 3).
+__device__ __forceinline__ float divide(float num, float d) {
+    const float r = __builtin_amdgcn_rcpf(d), q = num * r;
+    return fmaf(fmaf(-d, q, num), r, q);
+}
+// log1p(e) = 2 atanh(u), u = e / (2 + e) <= 1/3, by the series to u^15 (the
+// next term is 1.4e-9 of the sum).
+__device__ __forceinline__ float softplusf(float z) {
+    const float e = exp_minus_abs(z), u = divide(e, 2.0f + e), w = u * u;
+    float p = 1.0f / 15;
+    p = fmaf(p, w, 1.0f / 13);
+    p = fmaf(p, w, 1.0f / 11);
+    p = fmaf(p, w, 1.0f / 9);
+    p = fmaf(p, w, 1.0f / 7);
+    p = fmaf(p, w, 1.0f / 5);
+    p = fmaf(p, w, 1.0f / 3);
+    const float t = u + u;
+    return fmaxf(z, 0.0f) + fmaf(t * w, p, t);
+}
 __device__ __forceinline__ float sigmoidf(float z) {
-    const float e = expf(-fabsf(z));
-    return (z >= 0.0f ? 1.0f : e) / (1.0f + e);
+    const float e = exp_minus_abs(z);
+    return divide(z >= 0.0f ? 1.0f : e, 1.0f + e);
 }
 
 // Sum over a wavefront in a fixed order; the result in every lane.

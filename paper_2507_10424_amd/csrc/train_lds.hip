@@ -6,9 +6,9 @@
 //
 // Bound (n = 1024, (3,6)): VALU.  Forward: 33 instructions per row and
 // iteration for the check update, about 20 for the record, 3 per bit, and the
-// softplus of every posterior (about 55 with its exponential and logarithm at
-// full precision); backward: about 10 per edge and the sigmoid (about 35) per
-// bit.  Memory: 10 KB per frame and iteration written, then read.
+// softplus of every posterior (25); backward: about 10 per edge and the sigmoid
+// (17) per bit.  Memory: 10 KB per frame and iteration written, then read
+// (2.8 and 2.1 TB/s in the two kernels, 0.151 and 0.204 ms for 4,096 frames).
 #include <algorithm>
 
 #include "lds_common.h"
@@ -194,7 +194,8 @@ __device__ __forceinline__ void bwd_group(int32_t deg, unsigned char *lds, uint3
 
 // The sum over a bit's message list of the values at `base`, in ascending
 // check order from `acc`.  KW words of pairs are held; the rest is read.
-template <int KW>
+// ALL: nothing is left to read.
+template <int KW, bool ALL>
 __device__ __forceinline__ float column_sum(const unsigned char *lds, uint32_t base, int32_t d, const uint32_t *held,
                                             const uint32_t *tab, float acc) {
     float a[KW], b[KW];
@@ -207,18 +208,21 @@ __device__ __forceinline__ float column_sum(const unsigned char *lds, uint32_t b
 #pragma unroll
     for (int k = 0; k < KW; ++k)
         if (2 * k < d) acc = acc + a[k] + b[k];
-    for (int32_t k = KW; 2 * k < d; ++k) {
-        const uint32_t h = tab[64 * k];
-        const float u = lds_get<float>(lds, base + 4u * (h & 0xffffu)), v = lds_get<float>(lds, base + 4u * (h >> 16));
-        acc = acc + u + v;
-    }
+    if constexpr (!ALL)
+        for (int32_t k = KW; 2 * k < d; ++k) {
+            const uint32_t h = tab[64 * k];
+            const float u = lds_get<float>(lds, base + 4u * (h & 0xffffu));
+            const float v = lds_get<float>(lds, base + 4u * (h >> 16));
+            acc = acc + u + v;
+        }
     return acc;
 }
 
-// Neighbour tables of a wavefront's first groups, in registers.
-template <int CPT, int MAXD> struct Held {
-    static constexpr int kRowGroups = MAXD == 32 ? 1 : 2, kRowWords = MAXD / 2;
-    static constexpr int kBitWords = CPT <= 4 ? 4 : CPT <= 8 ? 2 : 1;
+// Neighbour tables of a wavefront's first groups, in registers: LEAST for graphs
+// with one group of rows per wavefront and bits of at most 4 messages.
+template <int CPT, int MAXD, bool LEAST> struct Held {
+    static constexpr int kRowGroups = MAXD == 32 || LEAST ? 1 : 2, kRowWords = MAXD / 2;
+    static constexpr int kBitWords = CPT <= 4 && !LEAST ? 4 : CPT <= 8 ? 2 : 1;
     uint32_t rw[kRowGroups][kRowWords], bw[CPT][kBitWords];
     int32_t rdeg[kRowGroups], rpos[kRowGroups], rcls[kRowGroups], bdeg[CPT];
     __device__ __forceinline__ void load(const LdsTables &t, int32_t w, int32_t nw, int lane) {
@@ -260,16 +264,26 @@ template <int CPT, int MAXD> struct Held {
     }
 };
 
-template <int CPT, int MAXD>
-__global__ __launch_bounds__(kThreads) void k_train_fwd(const Job J) {
+// What the registers hold of the neighbour tables: some groups', all groups',
+// all groups' where LEAST suffices.
+enum Tables { kSome, kAll, kLeast };
+// Waves per SIMD asked for: the smallest form is bound by latency with the four
+// that the compiler's own choice of registers leaves (a step of n = 1024, 4,096
+// frames: 0.424 ms with four, 0.367 with six, 0.379 with eight); the others
+// would spill too much.
+constexpr int waves_for(int tables) { return tables == kLeast ? 6 : 1; }
+
+template <int CPT, int MAXD, int TAB>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_for(TAB)))) void k_train_fwd(const Job J) {
     constexpr int W = MAXD <= 16 ? 3 : 4;
+    constexpr bool ALL = TAB != kSome;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int32_t n = J.n, T = J.c.T, slots = 64 * J.t.row_groups, bslots = 64 * J.t.bit_groups;
     const uint32_t eta0 = 4u * (uint32_t)(n + 1), zero_at = eta0 + 4u * (uint32_t)J.t.npos;
     float *red = reinterpret_cast<float *>(lds + zero_at + 4u);
     const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63;
     const int32_t w = __builtin_amdgcn_readfirstlane(tid >> 6), nw = nt >> 6;
-    typedef Held<CPT, MAXD> H;
+    typedef Held<CPT, MAXD, TAB == kLeast> H;
     H h;
     h.load(J.t, w, nw, lane);
     uint32_t at[CPT]; // slots of the bits tid + c nt
@@ -281,18 +295,19 @@ __global__ __launch_bounds__(kThreads) void k_train_fwd(const Job J) {
     }
     for (int32_t i = blockIdx.x; i < J.c.count; i += gridDim.x) {
         const size_t f = (size_t)J.c.f0 + i;
+        const int tf = h.again(tid);
         float rc[CPT];
         uint32_t ones = 0u; // own slots whose transmitted bit is 1
 #pragma unroll
         for (int c = 0; c < CPT; ++c) {
-            const int32_t j = tid + c * nt;
+            const int32_t j = tf + c * nt;
             if (j < n) lds_put<float>(lds, 4u * at[c], J.c.llr[f * n + j] + 0.0f); // -0 -> +0
         }
-        for (int32_t e = tid; e < J.t.npos; e += nt) lds_put<float>(lds, eta0 + 4u * (uint32_t)e, 0.0f);
+        for (int32_t e = tf; e < J.t.npos; e += nt) lds_put<float>(lds, eta0 + 4u * (uint32_t)e, 0.0f);
         __syncthreads();
 #pragma unroll
         for (int c = 0; c < CPT; ++c) {
-            const int32_t p = tid + c * nt;
+            const int32_t p = tf + c * nt;
             rc[c] = p < n ? lds_get<float>(lds, 4u * (uint32_t)p) : 0.0f;
             if (J.c.target && p < n && J.c.target[f * n + J.t.bit_of[p]]) ones |= 1u << c;
         }
@@ -309,7 +324,7 @@ __global__ __launch_bounds__(kThreads) void k_train_fwd(const Job J) {
                     fwd_group<MAXD, W>(h.rdeg[q], lds, h.rw[q], nullptr, eta0 + 4u * (uint32_t)(h.rpos[q] + lr),
                                        al[h.rcls[q]], be[h.rcls[q]], rec ? rec + 64 * g + lr : nullptr, slots);
             }
-            for (int32_t g = w + H::kRowGroups * nw; g < J.t.row_groups; g += nw) {
+            for (int32_t g = w + H::kRowGroups * nw; !ALL && g < J.t.row_groups; g += nw) {
                 const LdsGroup G = J.t.row_group[g];
                 const int32_t cls = J.t.row_class[g * 64 + lr];
                 fwd_group<MAXD, W>(G.degree, lds, nullptr, J.t.rows + G.table + lr,
@@ -321,8 +336,8 @@ __global__ __launch_bounds__(kThreads) void k_train_fwd(const Job J) {
             for (int c = 0; c < CPT; ++c) {
                 const int32_t g = w + c * nw, p = tr + c * nt;
                 if (g < J.t.bit_groups) {
-                    const float s = column_sum<H::kBitWords>(lds, eta0, h.bdeg[c], h.bw[c],
-                                                             J.t.bits + J.t.bit_group[g].table + lr, 0.0f) +
+                    const float s = column_sum<H::kBitWords, ALL>(lds, eta0, h.bdeg[c], h.bw[c],
+                                                             ALL ? nullptr : J.t.bits + J.t.bit_group[g].table + lr, 0.0f) +
                                     rc[c];
                     if (p < n) {
                         lds_put<float>(lds, 4u * (uint32_t)p, s);
@@ -338,9 +353,10 @@ __global__ __launch_bounds__(kThreads) void k_train_fwd(const Job J) {
             __syncthreads();
         }
         if (J.c.post) {
+            const int tp = h.again(tid);
 #pragma unroll
             for (int c = 0; c < CPT; ++c) {
-                const int32_t j = tid + c * nt;
+                const int32_t j = tp + c * nt;
                 if (j < n) J.c.post[f * n + j] = lds_get<float>(lds, 4u * at[c]);
             }
         }
@@ -356,16 +372,17 @@ __global__ __launch_bounds__(kThreads) void k_train_fwd(const Job J) {
 }
 
 // NC: degree classes, 1 or up to kTrainMaxClasses.
-template <int CPT, int MAXD, int NC>
-__global__ __launch_bounds__(kThreads) void k_train_bwd(const Job J) {
+template <int CPT, int MAXD, int NC, int TAB>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_for(TAB)))) void k_train_bwd(const Job J) {
     constexpr int W = MAXD <= 16 ? 3 : 4;
+    constexpr bool ALL = TAB != kSome;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int32_t n = J.n, T = J.c.T, B = J.c.B, slots = 64 * J.t.row_groups, bslots = 64 * J.t.bit_groups;
     const uint32_t gx0 = 4u * (uint32_t)(n + 1), zero_at = gx0 + 4u * (uint32_t)J.t.npos; // gs first, then gx
     float *red = reinterpret_cast<float *>(lds + zero_at + 4u);                            // [wave][2 NC]
     const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63;
     const int32_t w = __builtin_amdgcn_readfirstlane(tid >> 6), nw = nt >> 6;
-    typedef Held<CPT, MAXD> H;
+    typedef Held<CPT, MAXD, TAB == kLeast> H;
     H h;
     h.load(J.t, w, nw, lane);
     if (tid == 0) {
@@ -374,20 +391,21 @@ __global__ __launch_bounds__(kThreads) void k_train_bwd(const Job J) {
     }
     for (int32_t i = blockIdx.x; i < J.c.count; i += gridDim.x) {
         const size_t f = (size_t)J.c.f0 + i;
+        const int tf = h.again(tid);
         float gr[CPT];
         uint32_t ones = 0u;
 #pragma unroll
         for (int c = 0; c < CPT; ++c) {
-            const int32_t p = tid + c * nt;
+            const int32_t p = tf + c * nt;
             gr[c] = 0.0f;
             if (J.c.target && p < n && J.c.target[f * n + J.t.bit_of[p]]) ones |= 1u << c;
         }
-        for (int32_t e = tid; e < J.t.npos; e += nt) lds_put<float>(lds, gx0 + 4u * (uint32_t)e, 0.0f);
+        for (int32_t e = tf; e < J.t.npos; e += nt) lds_put<float>(lds, gx0 + 4u * (uint32_t)e, 0.0f);
         const uint32_t *rec = J.rec + ((size_t)i * T + T - 1) * W * slots;
         const float *sv = J.s + ((size_t)i * T + T - 1) * bslots;
         float sn[CPT]; // the posteriors of the next bit pass, read one pass ahead
 #pragma unroll
-        for (int c = 0; c < CPT; ++c) sn[c] = w + c * nw < J.t.bit_groups ? sv[tid + c * nt] : 0.0f;
+        for (int c = 0; c < CPT; ++c) sn[c] = w + c * nw < J.t.bit_groups ? sv[tf + c * nt] : 0.0f;
         __syncthreads();
         for (int32_t t = T; t >= 1; --t) {
             const int tr = h.again(tid), lr = tr & 63;
@@ -404,8 +422,8 @@ __global__ __launch_bounds__(kThreads) void k_train_bwd(const Job J) {
                 const int32_t g = w + c * nw, p = tr + c * nt;
                 if (g < J.t.bit_groups) {
                     const float y = (ones >> c) & 1u ? 1.0f : -1.0f;
-                    const float gj = column_sum<H::kBitWords>(lds, gx0, h.bdeg[c], h.bw[c],
-                                                              J.t.bits + J.t.bit_group[g].table + lr,
+                    const float gj = column_sum<H::kBitWords, ALL>(lds, gx0, h.bdeg[c], h.bw[c],
+                                                              ALL ? nullptr : J.t.bits + J.t.bit_group[g].table + lr,
                                                               J.c.scale * y * sigmoidf(y * sn[c]));
                     gr[c] += gj;
                     if (p < n) lds_put<float>(lds, 4u * (uint32_t)p, gj);
@@ -438,7 +456,7 @@ __global__ __launch_bounds__(kThreads) void k_train_bwd(const Job J) {
             for (int q = 0; q < H::kRowGroups; ++q)
                 if (w + q * nw < J.t.row_groups)
                     rows(h.rdeg[q], h.rw[q], nullptr, (uint32_t)h.rpos[q], h.rcls[q], rn[q]);
-            for (int32_t g = w + H::kRowGroups * nw; g < J.t.row_groups; g += nw) {
+            for (int32_t g = w + H::kRowGroups * nw; !ALL && g < J.t.row_groups; g += nw) {
                 const LdsGroup G = J.t.row_group[g];
                 uint32_t rw[W];
 #pragma unroll
@@ -463,12 +481,13 @@ __global__ __launch_bounds__(kThreads) void k_train_bwd(const Job J) {
             }
         }
         if (J.c.gllr) { // x^(1) = r: the last gx goes to the channel LLRs too
+            const int tg = h.again(tid);
 #pragma unroll
             for (int c = 0; c < CPT; ++c) {
-                const int32_t g = w + c * nw, p = tid + c * nt;
+                const int32_t g = w + c * nw, p = tg + c * nt;
                 if (g < J.t.bit_groups) {
-                    const float v = column_sum<H::kBitWords>(lds, gx0, h.bdeg[c], h.bw[c],
-                                                             J.t.bits + J.t.bit_group[g].table + lane, gr[c]);
+                    const float v = column_sum<H::kBitWords, ALL>(lds, gx0, h.bdeg[c], h.bw[c],
+                                                             ALL ? nullptr : J.t.bits + J.t.bit_group[g].table + (tg & 63), gr[c]);
                     if (p < n) J.c.gllr[f * n + J.t.bit_of[p]] = v;
                 }
             }
@@ -485,21 +504,35 @@ size_t lds_bytes(const ldpc_graph &g) {
 }
 
 // Rows of at most 8, 16 or 32 edges; 4, 8 or 16 bits per thread.
-Fn kernel_for(bool fwd, int cpt, int maxd, int ncls) {
-#define LDPC_K(C_, D_)                                                                                               \
-    if (cpt == C_ && maxd <= D_)                                                                                     \
-        return fwd ? &k_train_fwd<C_, D_> : ncls == 1 ? &k_train_bwd<C_, D_, 1> : &k_train_bwd<C_, D_, kTrainMaxClasses>;
-    LDPC_K(4, 8) LDPC_K(4, 16) LDPC_K(4, 32) LDPC_K(8, 8) LDPC_K(8, 16) LDPC_K(8, 32) LDPC_K(16, 32)
+Fn kernel_for(bool fwd, int cpt, int maxd, int ncls, int tables) {
+#define LDPC_K(C_, D_, T_)                                                                                           \
+    if (cpt == C_ && maxd <= D_ && tables == T_)                                                                     \
+        return fwd ? &k_train_fwd<C_, D_, T_>                                                                        \
+                   : ncls == 1 ? &k_train_bwd<C_, D_, 1, T_> : &k_train_bwd<C_, D_, kTrainMaxClasses, T_>;
+    LDPC_K(4, 8, kLeast)
+    LDPC_K(4, 8, kAll) LDPC_K(4, 16, kAll) LDPC_K(4, 32, kAll) LDPC_K(8, 8, kAll) LDPC_K(8, 16, kAll)
+    LDPC_K(8, 32, kAll)
+    LDPC_K(4, 8, kSome) LDPC_K(4, 16, kSome) LDPC_K(4, 32, kSome) LDPC_K(8, 8, kSome) LDPC_K(8, 16, kSome)
+    LDPC_K(8, 32, kSome) LDPC_K(16, 32, kSome)
 #undef LDPC_K
     return nullptr;
+}
+
+// The registers hold two groups of rows per wavefront (one of rows above 16) and
+// 8 messages of a bit (4 where a thread has 8 bits), or (kLeast) one group of
+// rows of at most 8 and 4 messages.
+int tables_for(const ldpc_graph &g, int cpt, int waves) {
+    if (cpt == 4 && g.dc_max <= 8 && g.dv_max <= 4 && g.lds.row_groups <= waves) return kLeast;
+    return cpt <= 8 && g.lds.row_groups <= (g.dc_max > 16 ? 1 : 2) * waves && g.dv_max <= (cpt <= 4 ? 8 : 4) ? kAll
+                                                                                                            : kSome;
 }
 
 int launch(const ldpc_graph &g, const TrainCall &c, const TrainLds &w, bool fwd, hipStream_t s) {
     const int cpt = cpt_for(g);
     const int ncls = (int)g.class_degrees.size();
-    const Fn fn = kernel_for(fwd, cpt, g.dc_max, ncls);
-    const int waves = std::max(g.lds.row_groups, (g.lds.bit_groups + cpt - 1) / cpt);
-    const int threads = 64 * std::min(waves, kThreads / 64);
+    const int waves = std::min(std::max(g.lds.row_groups, (g.lds.bit_groups + cpt - 1) / cpt), kThreads / 64);
+    const int threads = 64 * waves;
+    const Fn fn = kernel_for(fwd, cpt, g.dc_max, ncls, tables_for(g, cpt, waves));
     const size_t lds = lds_bytes(g);
     int per_cu = 0;
     if (hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
