@@ -22,7 +22,7 @@
 // frame-iteration through the Infinity Cache instead, two launches each, and
 // runs a tile of 64 frames until its last one stops.  Whole calls, streaming
 // before and this kernel now: n = 8176, rows of 32, 1,500 frames, 2.78 ms and
-// 0.276 ms; n = 4000, rows of 2 to 14, 777 frames, 1.57 and 0.209 ms; the
+// 0.276 ms; n = 4000, rows of 2 to 14, 777 frames, 1.57 and 0.162 ms; the
 // (3,6) code of n = 4096, 333 frames, 20 iterations, 0.340 and 0.071 ms.
 //
 // Row arithmetic, order of the sums, tests and outputs are those of the
@@ -505,12 +505,18 @@ int lds_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, uint
         return true;
     };
     if (!choose(1)) return LDPC_EHIP;
-    // Two frames per workgroup once one per workgroup fills the GPU: the LDS
-    // moves a pair of frames for little more than one, but a frame alone
-    // finishes sooner (n = 500, irregular: 1,000 frames 0.099 ms with one and
-    // 0.116 with two, 2,000 frames 0.193 and 0.147).
+    // Two frames per workgroup where many frames wait for each: the LDS moves a
+    // pair of frames for little more than one, but a frame alone finishes
+    // sooner and is replaced at less cost.  Where one workgroup fills a CU and
+    // rows are short, at once ((3,6) n = 4096, 1,500 frames: 0.158 ms with one
+    // and 0.143 with two); with rows above 8 (whose kernel for two spills) and
+    // with four workgroups per CU and more, late (irregular n = 4000: 777 frames
+    // 0.180 and 0.256 ms, 6,000 frames 0.806 and 0.814; (4,8) n = 600: 15,000
+    // frames 0.642 and 0.766; (5,10) n = 1000, 15,000 frames that do not
+    // converge: 2.17 and 1.77).
     int F = 1;
-    if (B > room && g.dc_max <= 16 && cpt <= 8 && lds_bytes(g, 2) <= (size_t)g.lds_max) {
+    const int64_t queued = g.dc_max > 8 ? 8 : room >= 4 * (int64_t)g.num_cu ? 32 : 1;
+    if (B > queued * room && g.dc_max <= 16 && cpt <= 8 && lds_bytes(g, 2) <= (size_t)g.lds_max) {
         F = 2;
         if (!choose(2)) return LDPC_EHIP;
     }

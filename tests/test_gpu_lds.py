@@ -102,6 +102,23 @@ def test_learned(name):
         assert_parity(tuple(t[some] for t in got), oracle_decode(H, llr[some], T, 0, alpha, beta), name)
 
 
+@pytest.mark.parametrize("learned", [False, True])
+def test_two_frames_with_long_rows(learned):
+    """Rows of up to 16 edges take two frames per workgroup from 8 frames per
+    resident workgroup on."""
+    H = _no_empty(CODES["irregular_2600"]())
+    llr = frames(H, 2600, seed=15)
+    note(f"[lds] two frames, long rows, learned={learned}")
+    a = b = None
+    if learned:
+        C, rng = np.unique(H.sum(1)).size, np.random.default_rng(3)
+        a = rng.uniform(0.6, 1.1, size=(9, C)).astype(np.float32)
+        b = rng.uniform(0.0, 0.3, size=(9, C)).astype(np.float32)
+    got = decode(H, llr, 9, 0, a, b)
+    some = slice(2000, 2010)
+    assert_parity(tuple(t[some] for t in got), oracle_decode(H, llr[some], 9, 0, a, b), "long rows")
+
+
 def test_more_frames_than_the_grid():
     """Frames beyond the first ones of every workgroup come from a counter."""
     H = CODES["wide_rows"]()
