@@ -497,12 +497,8 @@ int lds_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, uint
         fn = all && !(F == 2 && g.dc_max > 8) ? kernel_for<true>(F, cpt, g.dc_max, alpha != nullptr)
                                               : kernel_for<false>(F, cpt, g.dc_max, alpha != nullptr);
         lds = lds_bytes(g, F);
-        int per_cu = 0;
-        if (hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)fn, threads, lds) != hipSuccess)
-            return false;
-        room = (int64_t)std::max(per_cu, 1) * g.num_cu;
-        return true;
+        room = resident_workgroups((const void *)fn, threads, lds, g);
+        return room > 0;
     };
     if (!choose(1)) return LDPC_EHIP;
     // Two frames per workgroup where many frames wait for each: the LDS moves a

@@ -93,15 +93,6 @@ int pick(const ldpc_graph &g) {
     return -1;
 }
 
-// Resident workgroups of a kernel on the whole GPU (at least one per CU); -1 on failure.
-int64_t room_of(const void *fn, int threads, size_t lds, int num_cu) {
-    int per_cu = 0;
-    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess)
-        return -1;
-    return (int64_t)std::max(per_cu, 1) * num_cu;
-}
-
 // Layout variants whose two-slot kernel takes more than 128 registers, so that
 // at most three of its waves share a SIMD: their one-slot form is the faster
 // one at every batch size (n = 1152, rows of 9, 20,000 frames: 0.406 ms with
@@ -119,8 +110,8 @@ int kernel_of(const ldpc_graph &g, int64_t B, bool learned) {
     const int v = pick(g), o = v >= 0 ? one_slot(v) : -1;
     if (o < 0 || g.tuned() || !variant_ok(g, o)) return v;
     if (one_slot_always(v)) return o;
-    const int64_t room = room_of((const void *)kKernelsOne[learned ? 1 : 0][o - kNumVariants],
-                                 threads_for(g, kVariants[o]), lds_of(g, o), g.num_cu);
+    const int64_t room = resident_workgroups((const void *)kKernelsOne[learned ? 1 : 0][o - kNumVariants],
+                                             threads_for(g, kVariants[o]), lds_of(g, o), g);
     return B <= 4 * room ? o : v;
 }
 KernelFn kernel_fn(const ldpc_graph &g, int v, bool learned) {
@@ -174,11 +165,11 @@ void deal(Job &J, int grid) {
 
 // Grid of a persistent launch: every CU filled to its occupancy, but no more
 // workgroups than there are groups of `per_wg` frames.
-int launch_grid(const void *fn, int threads, size_t lds, int num_cu, int64_t frames, int cap_per_cu, int *grid,
-                int per_wg) {
-    int64_t want = room_of(fn, threads, lds, num_cu);
+int launch_grid(const void *fn, int threads, size_t lds, const ldpc_graph &g, int64_t frames, int cap_per_cu,
+                int *grid, int per_wg) {
+    int64_t want = resident_workgroups(fn, threads, lds, g);
     if (want < 0) return LDPC_EHIP;
-    if (cap_per_cu > 0) want = std::min(want, (int64_t)num_cu * cap_per_cu);
+    if (cap_per_cu > 0) want = std::min(want, (int64_t)g.num_cu * cap_per_cu);
     const int64_t groups = (frames + per_wg - 1) / per_wg;
     *grid = (int)(want < groups ? want : groups);
     if (*grid < 1) *grid = 1;
@@ -308,7 +299,7 @@ int onchip_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, u
     const int threads = threads_for(g, kVariants[v]), per_wg = v >= kNumVariants ? 1 : 2 * kVariants[v].f;
     const size_t lds = lds_of(g, v);
     int grid = 0;
-    int st = launch_grid((const void *)fn, threads, lds, g.num_cu, B, g.tuned() ? g.tuning.wg_per_cu : 0, &grid,
+    int st = launch_grid((const void *)fn, threads, lds, g, B, g.tuned() ? g.tuning.wg_per_cu : 0, &grid,
                          per_wg);
     if (st) return st;
     const int32_t early = test_period(flags);
@@ -345,14 +336,14 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
     int threads = 64;
     size_t lds = 0;
     int64_t frames = 0;
-    int num_cu = 0;
+    const ldpc_graph *any = nullptr; // one of the shared launch's
     uint32_t *queues = (uint32_t *)ws;
     struct Own {
         Job J;
         KernelFn fn;
         int threads;
         size_t lds;
-        int num_cu;
+        const ldpc_graph *g;
         int wg_per_cu; // tuned cap, 0 for none
     };
     std::vector<Own> own;
@@ -375,7 +366,7 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
         const size_t l_own = lds_of(g, v_own);
         bool alone = !shared_launch_ok(v);
         if (!alone) {
-            const int64_t room = room_of((const void *)fn, t_own, l_own, g.num_cu);
+            const int64_t room = resident_workgroups((const void *)fn, t_own, l_own, g);
             if (room < 0) return LDPC_EHIP;
             const int64_t in_flight = room * kVariants[v_own].f;
             alone = (int64_t)jb.B >= kOwnLaunchRounds * in_flight;
@@ -383,14 +374,14 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
         if (alone) {
             own.push_back(Own{make_job(g, v_own, jb.llr_dev, jb.B, jb.bits_dev, jb.post_dev, jb.iters_dev, jb.ok_dev,
                                        nullptr, nullptr, queues + (size_t)k * kQueueWords),
-                              fn, t_own, l_own, g.num_cu, g.tuned() ? g.tuning.wg_per_cu : 0});
+                              fn, t_own, l_own, &g, g.tuned() ? g.tuning.wg_per_cu : 0});
             continue;
         }
         const int t = threads_for(g, kVariants[v]);
         threads = t > threads ? t : threads;
         lds = lds_of(g, v) > lds ? lds_of(g, v) : lds;
         frames += jb.B;
-        num_cu = g.num_cu;
+        any = &g;
         jt.job[nj++] = make_job(g, v, jb.llr_dev, jb.B, jb.bits_dev, jb.post_dev, jb.iters_dev, jb.ok_dev, nullptr,
                                 nullptr, queues + (size_t)k * kQueueWords);
     }
@@ -427,7 +418,7 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
             fr += own[b].J.B;
         }
         int grid = 0;
-        const int st = launch_grid((const void *)own[a].fn, t, l, own[a].num_cu, fr, own[a].wg_per_cu, &grid,
+        const int st = launch_grid((const void *)own[a].fn, t, l, *own[a].g, fr, own[a].wg_per_cu, &grid,
                                    ot.njobs == 1 && own[a].J.variant >= kNumVariants
                                        ? 1
                                        : 2 * kVariants[own[a].J.variant].f);
@@ -437,7 +428,7 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
     }
     if (frames > 0) {
         int grid = 0;
-        const int st = launch_grid((const void *)k_onchip_multi, threads, lds, num_cu, frames, 0, &grid, 4);
+        const int st = launch_grid((const void *)k_onchip_multi, threads, lds, *any, frames, 0, &grid, 4);
         if (st) return st;
         launches.push_back(Launch{k_onchip_multi, grid, threads, lds, jt});
     }

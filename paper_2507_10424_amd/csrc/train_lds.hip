@@ -534,11 +534,8 @@ int launch(const ldpc_graph &g, const TrainCall &c, const TrainLds &w, bool fwd,
     const int threads = 64 * waves;
     const Fn fn = kernel_for(fwd, cpt, g.dc_max, ncls, tables_for(g, cpt, waves));
     const size_t lds = lds_bytes(g);
-    int per_cu = 0;
-    if (hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)fn, threads, lds) != hipSuccess)
-        return LDPC_EHIP;
-    const int64_t room = (int64_t)std::max(per_cu, 1) * g.num_cu;
+    const int64_t room = resident_workgroups((const void *)fn, threads, lds, g);
+    if (room < 0) return LDPC_EHIP;
     Job J{};
     J.t = LdsTables{g.lds.rows, g.lds.bits, g.lds.row_group, g.lds.bit_group, g.lds.slot_of, g.lds.bit_of,
                     g.lds.row_class, g.lds.row_groups, g.lds.bit_groups, g.lds.npos};

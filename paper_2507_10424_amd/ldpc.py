@@ -136,11 +136,27 @@ def load_library():
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# torch's current stream as a number, without the Stream object that
+# torch.cuda.current_stream builds around it (0.2 us instead of 2).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(device):
+    if _raw_stream is not None:
+        return ctypes.c_void_p(_raw_stream(torch.cuda.current_device() if device.index is None else device.index))
     return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+
+
+def _on(device, fn, *args):
+    """fn(*args) with `device` current (it mostly is already, and then the
+    guard would cost more than it does)."""
+    if device.index is None or device.index == torch.cuda.current_device():
+        return fn(*args)
+    with torch.cuda.device(device):
+        return fn(*args)
 
 
 class Graph:
@@ -218,14 +234,11 @@ def minsum_decode(g: Graph, llr: torch.Tensor, max_iter: int, flags: int = 0, wa
     llr = _check_llr(g, llr)
     B = llr.shape[0]
     bits, post, iters, ok = out if out is not None else _outputs(B, g.n, llr.device, want_post)
-    need = workspace_bytes(g, B, flags)
     if workspace is None:
-        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=llr.device)
+        workspace = torch.empty(max(workspace_bytes(g, B, flags), 1), dtype=torch.uint8, device=llr.device)
     lib = load_library()
-    with torch.cuda.device(llr.device):
-        st = lib.ldpc_minsum_decode(g.handle, _ptr(llr), B, int(max_iter), int(flags), _ptr(bits), _ptr(post),
-                                    _ptr(iters), _ptr(ok), _ptr(workspace), workspace.numel(),
-                                    _stream(llr.device))
+    st = _on(llr.device, lib.ldpc_minsum_decode, g.handle, _ptr(llr), B, int(max_iter), int(flags), _ptr(bits),
+             _ptr(post), _ptr(iters), _ptr(ok), _ptr(workspace), workspace.numel(), _stream(llr.device))
     if st:
         raise LdpcError(st, "ldpc_minsum_decode")
     return bits, post, iters, ok
@@ -243,9 +256,8 @@ def minsum_decode_noalloc(g: Graph, llr: torch.Tensor, max_iter: int, flags: int
     B = llr.shape[0]
     bits, post, iters, ok = out if out is not None else _outputs(B, g.n, llr.device, True)
     lib = load_library()
-    with torch.cuda.device(llr.device):
-        st = lib.ldpc_minsum_decode_noalloc(g.handle, _ptr(llr), B, int(max_iter), int(flags), _ptr(bits),
-                                            _ptr(post), _ptr(iters), _ptr(ok), _stream(llr.device))
+    st = _on(llr.device, lib.ldpc_minsum_decode_noalloc, g.handle, _ptr(llr), B, int(max_iter), int(flags), _ptr(bits),
+             _ptr(post), _ptr(iters), _ptr(ok), _stream(llr.device))
     if st:
         raise LdpcError(st, "ldpc_minsum_decode_noalloc")
     return bits, post, iters, ok
@@ -288,13 +300,11 @@ def nms_decode(g: Graph, llr: torch.Tensor, max_iter: int, alpha: torch.Tensor, 
     alpha = alpha.contiguous().float()
     beta = beta.contiguous().float()
     bits, post, iters, ok = out if out is not None else _outputs(B, g.n, llr.device, want_post)
-    need = workspace_bytes(g, B, flags)
     if workspace is None:
-        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=llr.device)
-    with torch.cuda.device(llr.device):
-        st = lib.ldpc_nms_decode(g.handle, _ptr(llr), B, int(max_iter), int(flags), _ptr(alpha), _ptr(beta), T,
-                                 _ptr(bits), _ptr(post), _ptr(iters), _ptr(ok), _ptr(workspace),
-                                 workspace.numel(), _stream(llr.device))
+        workspace = torch.empty(max(workspace_bytes(g, B, flags), 1), dtype=torch.uint8, device=llr.device)
+    st = _on(llr.device, lib.ldpc_nms_decode, g.handle, _ptr(llr), B, int(max_iter), int(flags), _ptr(alpha),
+             _ptr(beta), T, _ptr(bits), _ptr(post), _ptr(iters), _ptr(ok), _ptr(workspace), workspace.numel(),
+             _stream(llr.device))
     if st:
         raise LdpcError(st, "ldpc_nms_decode")
     return bits, post, iters, ok
