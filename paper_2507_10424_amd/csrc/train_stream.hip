@@ -8,7 +8,14 @@
 //
 // Bound: memory.  Per frame and iteration the forward moves 12 E + 8 n bytes of
 // messages and posteriors and 24 m of records (the previous messages come from
-// the previous record), the backward 16 E + 8 n and 12 m.
+// the previous record), the backward 16 E + 8 n and 12 m.  Lanes past the batch
+// load and store nothing (a last tile of 32 frames or fewer moves half the
+// lines), every load of a wavefront of the bit kernels is in flight before its
+// first add, and rows of at most 8 have a backward kernel of 50 registers (84
+// with the rows of 16): (3,6), n = 64,800, 96 frames, per launch and iteration,
+// before and after: bits 45 and 30 us, rows backward 61 and 49, rows forward
+// 53 and 48, 4.2 to 5.4 TB/s.  (Two rows per wavefront, 47 us, and a tile at a
+// time, whole step 1.638 ms against 1.634, gave nothing.)
 #include <algorithm>
 
 #include "train_internal.h"
@@ -169,7 +176,8 @@ __device__ __forceinline__ void row_fwd_long(int32_t d, const int32_t *__restric
     X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
 
 // One wavefront = one row x one tile, iteration t.
-__global__ __launch_bounds__(64 * kWaves) void k_rows_fwd(const Rows G, int32_t row_blocks, int32_t T, int32_t t,
+__global__ __launch_bounds__(64 * kWaves) void k_rows_fwd(const Rows G, int32_t row_blocks, int32_t f0, int32_t B,
+                                                          int32_t T, int32_t t,
                                                           const float *__restrict__ r, const float *__restrict__ s,
                                                           float *__restrict__ eta, uint32_t *__restrict__ rec,
                                                           const float *__restrict__ alpha,
@@ -178,7 +186,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_rows_fwd(const Rows G, int32_t 
     const int32_t tile = bid / row_blocks;
     const int32_t row = (bid % row_blocks) * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    if (row >= G.m) return;
+    if (row >= G.m || (int64_t)f0 + tile * kTile + lane >= B) return; // (lanes past the batch have no frame)
     const int32_t e0 = G.row_ptr[row], d = G.row_ptr[row + 1] - e0;
     if (d == 0) return;
     const int32_t c = G.row_class[row];
@@ -204,22 +212,56 @@ __global__ __launch_bounds__(64 * kWaves) void k_rows_fwd(const Rows G, int32_t 
     }
 }
 
-// The sum of a bit's column of `v` (edge order, ascending check) from acc.
-__device__ __forceinline__ float column(const int32_t *__restrict__ csc, int32_t k0, int32_t k1,
-                                        const float *__restrict__ v, float acc) {
-    for (int32_t k = k0; k < k1; k += 8) { // (the table has 8 entries of padding)
-        float x[8];
+// The columns of a wavefront's four bits: their bounds and the first 8 edges of
+// each, by scalar loads (both tables have 8 entries of padding, so that bits
+// past n have no edges).
+struct Columns {
+    int32_t k0[kColsPerWave], k1[kColsPerWave], idx[kColsPerWave][8];
+    __device__ __forceinline__ Columns(const int32_t *__restrict__ col_ptr, const int32_t *__restrict__ csc, int32_t c0) {
+        int32_t kp[kColsPerWave + 1];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            x[u] = 0.0f;
-            if (k + u < k1) x[u] = v[(size_t)csc[k + u] * kTile];
+        for (int c = 0; c <= kColsPerWave; ++c) kp[c] = col_ptr[c0 + c];
+#pragma unroll
+        for (int c = 0; c < kColsPerWave; ++c) {
+            k0[c] = kp[c];
+            k1[c] = kp[c + 1];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) idx[c][u] = csc[k0[c] + u];
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) asm volatile("" : "+v"(x[u])); // all loads before the first add
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc = k + u < k1 ? acc + x[u] : acc;
     }
-    return acc;
+    // Requests the first 8 values of every column of `v` (loads behind uniform
+    // branches, so a column of 3 issues 3).
+    __device__ __forceinline__ void load(const float *__restrict__ v, float x[kColsPerWave][8]) const {
+#pragma unroll
+        for (int c = 0; c < kColsPerWave; ++c)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                x[c][u] = 0.0f;
+                if (k0[c] + u < k1[c]) x[c][u] = v[(size_t)idx[c][u] * kTile];
+            }
+    }
+    // acc + the sum of column c in edge order (ascending check).
+    __device__ __forceinline__ float sum(int c, const int32_t *__restrict__ csc, const float *__restrict__ v,
+                                         const float x[8], float acc) const {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc = k0[c] + u < k1[c] ? acc + x[u] : acc;
+        for (int32_t k = k0[c] + 8; k < k1[c]; k += 8) {
+            float y[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) y[u] = v[(size_t)csc[k + u < k1[c] ? k + u : k] * kTile];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc = k + u < k1[c] ? acc + y[u] : acc;
+        }
+        return acc;
+    }
+};
+// Keeps the adds of the loaded values behind the last load (they stand under
+// the loads' own conditions, into whose branches the compiler would move them).
+__device__ __forceinline__ void all_loaded(float x[kColsPerWave][8]) {
+#pragma unroll
+    for (int c = 0; c < kColsPerWave; ++c)
+        asm volatile("" : "+v"(x[c][0]), "+v"(x[c][1]), "+v"(x[c][2]), "+v"(x[c][3]), "+v"(x[c][4]), "+v"(x[c][5]),
+                     "+v"(x[c][6]), "+v"(x[c][7]));
 }
 
 // s^(t) of four bits x one tile, and the loss of a workgroup's bits and frames.
@@ -240,13 +282,21 @@ __global__ __launch_bounds__(64 * kWaves) void k_bits_fwd(const int32_t *__restr
     const float *et = eta + (size_t)tile * E * kTile + lane, *rt = r + (size_t)tile * n * kTile + lane;
     float *st = s + ((size_t)tile * T + (t - 1)) * n * kTile + lane;
     float loss = 0.0f;
+    if (c0 < n && f < B) {
+        const Columns C(col_ptr, csc, c0);
+        float x[kColsPerWave][8], rv[kColsPerWave];
+        C.load(et, x);
 #pragma unroll
-    for (int c = 0; c < kColsPerWave; ++c) {
-        const int32_t j = c0 + c;
-        if (j >= n) break;
-        const float v = column(csc, col_ptr[j], col_ptr[j + 1], et, 0.0f) + rt[(size_t)j * kTile];
-        st[(size_t)j * kTile] = v;
-        if (f < B) loss += softplusf(target && target[f * n + j] ? v : -v);
+        for (int c = 0; c < kColsPerWave; ++c) rv[c] = rt[(size_t)min(c0 + c, n - 1) * kTile];
+        all_loaded(x);
+#pragma unroll
+        for (int c = 0; c < kColsPerWave; ++c) {
+            const int32_t j = c0 + c;
+            if (j >= n) break;
+            const float v = C.sum(c, csc, et, x[c], 0.0f) + rv[c];
+            st[(size_t)j * kTile] = v;
+            loss += softplusf(target && target[f * n + j] ? v : -v);
+        }
     }
     loss = wave_sum(loss);
     if (lane == 0) red[w] = loss;
@@ -276,6 +326,20 @@ __global__ __launch_bounds__(64 * kWaves) void k_bits_bwd(const int32_t *__restr
     const float *gt = gx + (size_t)tile * E * kTile + lane;
     const size_t bit0 = (size_t)tile * n * kTile + lane;
     const float *st = s + ((size_t)tile * T + (t > 0 ? t - 1 : 0)) * n * kTile + lane;
+    if (c0 >= n || f >= B) return;
+    const Columns C(col_ptr, csc, c0);
+    float x[kColsPerWave][8], sv[kColsPerWave];
+    if (t < T) {
+        C.load(gt, x);
+    } else {
+#pragma unroll
+        for (int c = 0; c < kColsPerWave; ++c)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[c][u] = 0.0f;
+    }
+#pragma unroll
+    for (int c = 0; c < kColsPerWave; ++c) sv[c] = st[(size_t)min(c0 + c, n - 1) * kTile];
+    all_loaded(x);
 #pragma unroll
     for (int c = 0; c < kColsPerWave; ++c) {
         const int32_t j = c0 + c;
@@ -283,12 +347,12 @@ __global__ __launch_bounds__(64 * kWaves) void k_bits_bwd(const int32_t *__restr
         const size_t o = bit0 + (size_t)j * kTile;
         float g = 0.0f;
         if (t > 0) {
-            const float y = target && f < B && target[f * n + j] ? 1.0f : -1.0f;
-            g = f < B ? scale * y * sigmoidf(y * st[(size_t)j * kTile]) : 0.0f;
+            const float y = target && target[f * n + j] ? 1.0f : -1.0f;
+            g = scale * y * sigmoidf(y * sv[c]);
         } else {
             g = gr[o];
         }
-        if (t < T) g = column(csc, col_ptr[j], col_ptr[j + 1], gt, g);
+        if (t < T) g = C.sum(c, csc, gt, x[c], g);
         if (t > 0) gs[o] = g;
         if (gr) gr[o] = t == T || t == 0 ? g : gr[o] + g;
     }
@@ -359,9 +423,11 @@ __device__ __forceinline__ void row_bwd_long(int32_t d, const int32_t *__restric
 }
 
 // kRowsPerWave rows x one tile of iteration t; the wavefront's sums for every
-// class go to gpart[2][T][ncls][waves].
-template <int NC>
-__global__ __launch_bounds__(64 * kWaves) void k_rows_bwd(const Rows G, int32_t row_blocks, int32_t T, int32_t t,
+// class go to gpart[2][T][ncls][waves].  MAXD: longest row of the graph that is
+// unrolled (its registers are every wavefront's).
+template <int NC, int MAXD>
+__global__ __launch_bounds__(64 * kWaves) void k_rows_bwd(const Rows G, int32_t row_blocks, int32_t f0, int32_t B,
+                                                          int32_t T, int32_t t,
                                                           const float *__restrict__ gs, float *__restrict__ gx,
                                                           const uint32_t *__restrict__ rec,
                                                           const float *__restrict__ alpha,
@@ -375,33 +441,37 @@ __global__ __launch_bounds__(64 * kWaves) void k_rows_bwd(const Rows G, int32_t 
     float ga[NC], gb[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) ga[c] = gb[c] = 0.0f;
-    for (int32_t row = row0; row < G.m && row < row0 + kRowsPerWave; ++row) {
-        const int32_t e0 = G.row_ptr[row], d = G.row_ptr[row + 1] - e0;
-        if (d == 0) continue;
-        const int32_t cls = G.row_class[row];
-        const float al = alpha[(t - 1) * ncls + cls], be = beta[(t - 1) * ncls + cls];
-        const float *gv = gs + (size_t)tile * G.n * kTile + lane;
-        float *xv = gx + ((size_t)tile * G.E + e0) * kTile + lane;
-        const uint32_t *rc =
-            rec + (((size_t)tile * T + (t - 1)) * G.m + row) * G.words * kTile + lane;
-        float a = 0.0f, b = 0.0f;
-        if (G.words > 3) {
-            row_bwd_long(d, G.col_idx + e0, gv, xv, rc, t == T, al, be, a, b);
-        } else {
-            switch (d) {
+    if ((int64_t)f0 + tile * kTile + lane < B) { // lanes past the batch keep sums of zero
+        for (int32_t row = row0; row < min(row0 + kRowsPerWave, G.m); ++row) {
+            const int32_t e0 = G.row_ptr[row], d = G.row_ptr[row + 1] - e0;
+            if (d == 0) continue;
+            const int32_t cls = G.row_class[row];
+            const float al = alpha[(t - 1) * ncls + cls], be = beta[(t - 1) * ncls + cls];
+            const float *gv = gs + (size_t)tile * G.n * kTile + lane;
+            float *xv = gx + ((size_t)tile * G.E + e0) * kTile + lane;
+            const uint32_t *rc =
+                rec + (((size_t)tile * T + (t - 1)) * G.m + row) * G.words * kTile + lane;
+            float a = 0.0f, b = 0.0f;
+            if (G.words > 3) {
+                row_bwd_long(d, G.col_idx + e0, gv, xv, rc, t == T, al, be, a, b);
+            } else {
+                switch (d) {
 #define LDPC_CASE(D)                                                                                                 \
-    case D: row_bwd<D>(G.col_idx + e0, gv, xv, rc, t == T, al, be, a, b); break;
-                LDPC_DEGREES(LDPC_CASE)
+                case D:                                                                                              \
+                    if constexpr (D <= MAXD) row_bwd<D>(G.col_idx + e0, gv, xv, rc, t == T, al, be, a, b);             \
+                    break;
+                    LDPC_DEGREES(LDPC_CASE)
 #undef LDPC_CASE
-            default: break;
+                default: break;
+                }
             }
-        }
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
-            if (NC == 1 || cls == c) {
-                ga[c] += a;
-                gb[c] += b;
-            }
+            for (int c = 0; c < NC; ++c)
+                if (NC == 1 || cls == c) {
+                    ga[c] += a;
+                    gb[c] += b;
+                }
+        }
     }
     float *out = gpart + (int64_t)(t - 1) * ncls * waves + wave0 + (int64_t)bid * kWaves + w;
 #pragma unroll
@@ -413,6 +483,14 @@ __global__ __launch_bounds__(64 * kWaves) void k_rows_bwd(const Rows G, int32_t 
             out[((int64_t)T * ncls + c) * waves] = b;
         }
     }
+}
+
+using BwdFn = void (*)(const Rows, int32_t, int32_t, int32_t, int32_t, int32_t, const float *, float *,
+                       const uint32_t *, const float *, const float *, int32_t, float *, int64_t, int64_t);
+// (rows of more than kMaxUnrolled are not unrolled at all)
+BwdFn bwd_for(const ldpc_graph &g, int32_t ncls) {
+    if (g.dc_max <= 8 || g.dc_max > kMaxUnrolled) return ncls == 1 ? &k_rows_bwd<1, 8> : &k_rows_bwd<kTrainMaxClasses, 8>;
+    return ncls == 1 ? &k_rows_bwd<1, kMaxUnrolled> : &k_rows_bwd<kTrainMaxClasses, kMaxUnrolled>;
 }
 
 int64_t tiles_of(int64_t frames) { return (frames + kTile - 1) / kTile; }
@@ -452,7 +530,8 @@ int train_stream_forward(const ldpc_graph &g, const TrainCall &c, const TrainStr
     k_tiles<<<nt * nchunks, 256, 0, st>>>(c.llr, c.f0, end, g.n, w.r);
     const int64_t parts = train_stream_loss_parts(g, c.B), part0 = (int64_t)(c.f0 / kTile) * cb;
     for (int32_t t = 1; t <= c.T; ++t) {
-        k_rows_fwd<<<nt * rb, 64 * kWaves, 0, st>>>(G, rb, c.T, t, w.r, w.s, w.eta, w.rec, c.alpha, c.beta, ncls);
+        k_rows_fwd<<<nt * rb, 64 * kWaves, 0, st>>>(G, rb, c.f0, end, c.T, t, w.r, w.s, w.eta, w.rec, c.alpha, c.beta,
+                                                    ncls);
         k_bits_fwd<<<nt * cb, 64 * kWaves, 0, st>>>(g.col_ptr, csc_of(g), g.n, g.E, cb, c.f0, end, c.T, t, w.r, w.eta,
                                                     w.s, c.target, w.loss_part + (t - 1) * parts + part0);
     }
@@ -471,9 +550,9 @@ int train_stream_backward(const ldpc_graph &g, const TrainCall &c, const TrainSt
     for (int32_t t = c.T; t >= 1; --t) {
         k_bits_bwd<<<nt * cb, 64 * kWaves, 0, st>>>(g.col_ptr, csc_of(g), g.n, g.E, cb, c.f0, end, c.T, t, w.eta, w.s,
                                                     c.target, c.scale, w.gs, gr);
-        auto *fn = ncls == 1 ? &k_rows_bwd<1> : &k_rows_bwd<kTrainMaxClasses>;
-        fn<<<nt * rb, 64 * kWaves, 0, st>>>(G, rb, c.T, t, w.gs, w.eta, w.rec, c.alpha, c.beta, ncls, w.gpart, waves,
-                                            wave0);
+        auto *fn = bwd_for(g, ncls);
+        fn<<<nt * rb, 64 * kWaves, 0, st>>>(G, rb, c.f0, end, c.T, t, w.gs, w.eta, w.rec, c.alpha, c.beta, ncls,
+                                            w.gpart, waves, wave0);
     }
     if (gr) {
         k_bits_bwd<<<nt * cb, 64 * kWaves, 0, st>>>(g.col_ptr, csc_of(g), g.n, g.E, cb, c.f0, end, c.T, 0, w.eta, w.s,

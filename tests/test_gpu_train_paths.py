@@ -126,3 +126,31 @@ def test_batches_in_passes(name, B, T, K):
         # B frames in another order: (B + T m) roundings of sums whose terms may cancel
         scale = float(torch.maximum(y.abs(), z.abs())[fine].max())
         assert float((x.double() - want)[fine].abs().max()) <= 2e-5 * scale
+
+
+STREAM_IRREGULAR = {
+    "rows_16_columns_12": lambda: _classes(wl.random_irregular_code(9001, 5500, seed=12, dv_choices=(2, 3, 12),
+                                                                   max_row_degree=16)),
+    "rows_8": lambda: _classes(wl.random_irregular_code(17003, 8500, seed=13, dv_choices=(1, 2, 3, 4),
+                                                        max_row_degree=8)),
+}
+
+
+@pytest.mark.parametrize("name", sorted(STREAM_IRREGULAR))
+def test_gradient_of_irregular_codes_in_device_memory(name):
+    """State in device memory with several row degrees, columns of more than 8
+    checks, a number of bits that is no multiple of 4 and one frame in the last
+    tile of 64 (the lanes without a frame hold NaNs in the workspace)."""
+    H = STREAM_IRREGULAR[name]()
+    m, n = H.shape
+    T, B = 3, 65
+    C = oracle.check_degrees(H).size
+    assert C > 1 and n % 4
+    a, b = _weights(T, C, 14)
+    llr = wl.bpsk_awgn_llr(None, 2.0, 0.4, seed=15, n=n, batch=B)
+    note(f"[train] {name} m={m} n={n} classes={C} B={B}")
+    loss, post, ga, gb, gl = _run(H, llr, a, b, 2)
+    ref = oracle.nms_train_grad_f32_forward(H, llr, a, b, llr_grad=True)
+    assert np.array_equal(post.astype(np.float64), ref["post"])
+    assert abs(loss - ref["loss"]) <= 2e-5 * abs(ref["loss"])
+    assert_grad_parity(H, T, B, {"galpha": ga, "gbeta": gb, "gllr": gl}, ref, name)
