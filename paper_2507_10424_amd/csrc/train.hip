@@ -24,7 +24,7 @@
 // a workgroup of 256 threads per frame, its state in LDS or in device memory,
 // that kept the messages of every ckpt_every-th iteration and ran the forward
 // again in between): n = 1024, 4,096 frames, T = 10: 1.97 -> 0.367 ms; n =
-// 64800, 96 frames, T = 10: 51.1 -> 2.10 ms.
+// 64800, 96 frames, T = 10: 51.1 -> 1.63 ms.
 #include <algorithm>
 
 #include "train_internal.h"
