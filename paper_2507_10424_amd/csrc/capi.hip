@@ -65,6 +65,9 @@ int decode(const ldpc_graph *g, const float *llr, int32_t B, int32_t L, uint32_t
     if (use_lds(*g, flags)) {
         // the workspace is the one that ldpc_decode_workspace_bytes asks for
         if (ws == nullptr || ws_bytes < ldpc_decode_workspace_bytes(g, B, flags)) return LDPC_EWORKSPACE;
+        // (regular graphs with rows of 8 and 10: regular_form in decode_onchip.hip)
+        if (ldpc::onchip_regular(*g))
+            return ldpc::onchip_decode(*g, llr, B, L, flags, alpha, beta, T, bits, post, iters, ok, ws, ws_bytes, stream);
         return ldpc::lds_decode(*g, llr, B, L, flags, alpha, beta, bits, post, iters, ok, ws, stream);
     }
     if (use_onchip(*g, flags)) {

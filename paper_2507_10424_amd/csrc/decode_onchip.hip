@@ -59,6 +59,14 @@ int threads_for(const ldpc_graph &g, const Variant &v) {
     return t < 64 ? 64 : t;
 }
 
+// Every column's degree is within the profile at any slot index.
+bool profile_holds(const ldpc_graph &g, const Variant &v) {
+    const int t = threads_for(g, v);
+    for (int c = 0; c * t < g.n; ++c)
+        if (c >= v.cpt || (int)((v.dvp >> (4 * c)) & 15u) < g.dv_max) return false;
+    return true;
+}
+
 bool variant_ok(const ldpc_graph &g, int k) {
     if (k < 0 || k >= kNumKernels) return false;
     const Variant &v = kVariants[k];
@@ -66,8 +74,10 @@ bool variant_ok(const ldpc_graph &g, int k) {
     // (a padded layout variant, cf & 4, takes columns of any degree up to its dv)
     const bool cols_ok = (v.cx && !(v.cf & 4)) ? (g.dv_min == v.dv && g.dv_max == v.dv) : g.dv_max <= v.dv;
     // the layout's tables are for their own geometry, stride and thread count
+    const bool regular = k >= kFirstRegular && k < kFirstOwnLayout; // on the tables without a profile
     const bool cf_ok = v.cf == 0 || (g.cf.edge != nullptr && g.cf.rpt == v.rpt && g.cf.cpt == v.cpt &&
-                                     g.cf.dvs == v.dv && g.cf.dvp == v.dvp && threads_for(g, v) == g.cf.nt);
+                                     g.cf.dvs == v.dv && g.cf.dvp == (regular ? 0u : v.dvp) &&
+                                     threads_for(g, v) == g.cf.nt && (!regular || profile_holds(g, v)));
     const size_t state = v.cf != 0 ? cf_state_bytes(g, v.f) : state_bytes(g, v.f);
     return rows_ok && cols_ok && cf_ok && threads_for(g, v) <= kMaxThreads && g.edge_tab != nullptr &&
            state + sizeof(Shared) + 1024 <= (size_t)g.lds_max;
@@ -101,6 +111,20 @@ constexpr bool one_slot_always(int v) {
     return v == 23 || v == 27 || v == 29 || v == 31 || v == 33 || v == 37 || v == 39 || v == 41;
 }
 
+// The kernel for a regular graph's own row and column degree, -1 if there is
+// none.  Faster at every batch size than the padded layout's kernels, which
+// read six messages (four with rows of 16) of any bit, and than the
+// LDS-resident decoder, which takes rows of 8 and 10 otherwise (20 iterations,
+// 300 and 16,000 frames, before and now: (3,9) n = 2,007 0.047 and 0.522 ms,
+// 0.026 and 0.457; (3,12) n = 2,004 0.036 and 0.320, 0.017 and 0.215; (4,16)
+// n = 2,016 0.037 and 0.409, 0.019 and 0.251; (4,8) n = 2,008 0.062 and 1.389,
+// 0.042 and 0.701; (5,10) n = 1,010 0.049 and 1.028, 0.034 and 0.572).
+int regular_form(const ldpc_graph &g) {
+    for (int k = kFirstRegular; k < kNumKernels; ++k)
+        if (variant_ok(g, k)) return k;
+    return -1;
+}
+
 // The kernel (index into kVariants) that decodes B frames: the picked variant,
 // or, without a tuning record, its one-slot form, whose rounds are about half
 // as long, while no more than four frames fall to each resident workgroup of
@@ -108,7 +132,8 @@ constexpr bool one_slot_always(int v) {
 // 4,000: 0.097 and 0.092; 20,000: 0.233 and 0.253).
 int kernel_of(const ldpc_graph &g, int64_t B, bool learned) {
     const int v = pick(g), o = v >= 0 ? one_slot(v) : -1;
-    if (o < 0 || g.tuned() || !variant_ok(g, o)) return v;
+    if (onchip_regular(g)) return regular_form(g);
+    if (g.tuned() || o < 0 || !variant_ok(g, o)) return v;
     if (one_slot_always(v)) return o;
     const int64_t room = resident_workgroups((const void *)kKernelsOne[learned ? 1 : 0][o - kNumVariants],
                                              threads_for(g, kVariants[o]), lds_of(g, o), g);
@@ -222,7 +247,8 @@ bool onchip_cf_geometry(const ldpc_graph &g, const std::vector<int32_t> &col_deg
     std::sort(sorted.begin(), sorted.end());
     int best = -1;
     int64_t best_cost = 0;
-    for (int k = 0; k < kNumVariants; ++k) {
+    for (int k = 0; k < kNumKernels; ++k) {
+        if (k >= kNumVariants && k < kFirstOwnLayout) continue; // (on the tables of the others)
         const Variant &v = kVariants[k];
         if (v.cf == 0 || g.dc_min != g.dc_max || g.dc_max != v.dc || g.dv_max > v.dv) continue;
         if (!(v.cf & 4) && (g.dv_min != v.dv || g.dv_max != v.dv)) continue; // exact columns only
@@ -251,6 +277,10 @@ bool onchip_cf_geometry(const ldpc_graph &g, const std::vector<int32_t> &col_deg
     *dvs = kVariants[best].dv;
     *dvp = kVariants[best].dvp;
     return true;
+}
+
+bool onchip_regular(const ldpc_graph &g) {
+    return g.edge_tab != nullptr && !g.tuned() && regular_form(g) >= 0;
 }
 
 bool onchip_fits(const ldpc_graph &g) { return g.edge_tab != nullptr && pick(g) >= 0; }
@@ -292,7 +322,7 @@ int onchip_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, u
                   const float *beta, int32_t T, uint8_t *bits, float *post, int32_t *iters, uint8_t *ok, void *ws,
                   size_t ws_bytes, hipStream_t stream) {
     (void)T;
-    if (!onchip_fits(g)) return LDPC_EUNSUPPORTED;
+    if (!onchip_fits(g) && !onchip_regular(g)) return LDPC_EUNSUPPORTED;
     if (ws == nullptr || ws_bytes < onchip_workspace_bytes(g, B)) return LDPC_EWORKSPACE;
     const int v = kernel_of(g, B, alpha != nullptr);
     const KernelFn fn = kernel_fn(g, v, alpha != nullptr);

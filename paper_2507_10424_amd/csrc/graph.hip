@@ -317,8 +317,11 @@ int build(const uint8_t *H, int32_t m, int32_t n, hipStream_t s, ldpc_graph *g) 
             ldpc::OnchipLayout lay;
             int32_t rpt = 0, cpt = 0, dvs = 0;
             uint32_t dvp = 0;
+            // (rows of 8 and 10 with a tenth of the search: (4,8) n = 2,008, a build
+            // of 0.10 s instead of 0.94 for decodes that take 1 % longer)
+            const int32_t moves = g->dc_max == 8 || g->dc_max == 10 ? 300 : 3000;
             if (E > 0 && g->dc_min == g->dc_max && ldpc::onchip_cf_geometry(*g, h_col, &rpt, &cpt, &dvs, &dvp) &&
-                ldpc::onchip_cf_layout(h_rowptr, h_bit, h_class, m, n, rpt, cpt, dvs, dvp, &lay)) {
+                ldpc::onchip_cf_layout(h_rowptr, h_bit, h_class, m, n, rpt, cpt, dvs, dvp, &lay, moves)) {
                 const size_t S = (size_t)lay.rpt * lay.nt;
                 if (dalloc(&g->cf.edge, lay.edge.size()) != hipSuccess ||
                     dalloc(&g->cf.bitpos, lay.bitpos.size()) != hipSuccess ||

@@ -105,7 +105,7 @@ std::vector<int32_t> bipartite_edge_colour(int32_t nleft, int32_t nright, const 
 
 bool onchip_cf_layout(const std::vector<int32_t> &rowptr, const std::vector<int32_t> &col,
                       const std::vector<int32_t> &row_class, int32_t m, int32_t n, int32_t rpt, int32_t cpt,
-                      int32_t dvs, uint32_t dvp, OnchipLayout *out) {
+                      int32_t dvs, uint32_t dvp, OnchipLayout *out, int32_t moves_per_row) {
         const int64_t E = (int64_t)col.size();
     if (m < 1 || n < 1 || E < 1 || n >= 65536 || E >= 65536 || rpt < 1 || cpt < 1) return false;
     int32_t dc = 0;
@@ -174,7 +174,7 @@ bool onchip_cf_layout(const std::vector<int32_t> &rowptr, const std::vector<int3
         return delta;
     };
     std::vector<std::pair<int64_t, int32_t>> ch;
-    const int64_t moves = std::min<int64_t>(3000000, 3000 * (int64_t)m);
+    const int64_t moves = std::min<int64_t>(3000000, moves_per_row * (int64_t)m);
     for (int64_t it = 0; it < moves; ++it) {
         ch.clear();
         const bool rowmove = (it & 1) == 0 || n < 2;

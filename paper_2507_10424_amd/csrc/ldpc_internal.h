@@ -131,6 +131,9 @@ bool onchip_fits(const ldpc_graph &g);
 // Whether the on-chip path would decode the graph with masked rows, where the
 // LDS-resident decoder is faster.
 bool onchip_masks_rows(const ldpc_graph &g);
+// Whether a graph without a tuning record has a kernel for its own row and
+// column degree (some such graphs fit no variant of the tuning record).
+bool onchip_regular(const ldpc_graph &g);
 bool onchip_variant_fits(const ldpc_graph &g, int variant);
 int onchip_num_variants();
 // Whether the kernel of (variant, register budget) needs no scratch (no spills).
@@ -162,7 +165,7 @@ struct OnchipLayout {
 };
 bool onchip_cf_layout(const std::vector<int32_t> &rowptr, const std::vector<int32_t> &col,
                       const std::vector<int32_t> &row_class, int32_t m, int32_t n, int32_t rpt, int32_t cpt,
-                      int32_t dvs, uint32_t dvp, OnchipLayout *out);
+                      int32_t dvs, uint32_t dvp, OnchipLayout *out, int32_t moves_per_row = 3000);
 // The layout geometry the on-chip variants offer for a graph (rows of one
 // degree): rows and bits per thread, bit-side stride and column degree
 // profile; false if none fits.

@@ -738,7 +738,15 @@ constexpr Variant kVariants[] = {
     {6, true, 6, true, 2, 4, 1, 6},               {6, true, 6, true, 1, 2, 1, 6},
     {9, true, 6, true, 2, 6, 1, 6},               {12, true, 6, true, 1, 4, 1, 6},
     {16, true, 4, true, 1, 6, 1, 6},
+    // One-slot forms that read each column's own messages where all columns
+    // have one degree: on the tables of the padded layout of rows of 9, 12
+    // and 16 (their bit-side profile names one degree for every slot index
+    // in use), then rows of 8 and 10 in a layout of their own.
+    {9, true, 6, true, 2, 6, 1, 6, 0x333333u},    {12, true, 6, true, 1, 4, 1, 6, 0x3333u},
+    {16, true, 4, true, 1, 6, 1, 6, 0x4444u},     {8, true, 4, true, 2, 4, 1, 2},
+    {10, true, 5, true, 2, 4, 1, 2},
 };
+constexpr int kFirstRegular = 53, kFirstOwnLayout = 56;
 constexpr int kNumKernels = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
 constexpr int kNumVariants = 42; // of the tuning record
 // The one-slot form of a variant, -1 if it has none.
