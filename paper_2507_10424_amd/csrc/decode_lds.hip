@@ -210,7 +210,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_lds(const LdsJob J, int32_t L, 
     const int32_t dealt = (int32_t)gridDim.x * F, left = B - dealt; // frames past the first ones: from the counters
     // thread 0: the next frame of a slot
     auto draw = [&](int32_t &hc, uint32_t &dead) {
-        return J.queue ? dealt + take_frame(J.queue, left, J.nq, hc, dead) : B;
+        return J.queue ? dealt + take_frame<false>(J.queue, left, J.nq, hc, dead) : B;
     };
     int32_t fr[F], tt[F], ph[F];                       // ph: (tt - 1) modulo the test period
     V rc[CPT], rnx[CPT];                               // channel LLRs: own slots, next frame's own bits

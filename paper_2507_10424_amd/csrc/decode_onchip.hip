@@ -171,21 +171,28 @@ Job make_job(const ldpc_graph &g, int variant, const float *llr, int32_t B, uint
     J.beta = beta;
     J.ncls = (int32_t)g.class_degrees.size();
     J.variant = variant;
-    J.dealt = 0;
+    J.dealt = J.grid = J.rounds = 0;
     J.queue = queue;
     J.nq = queues_for(B);
     return J;
 }
 
 // A launch of `grid` workgroups for one job with a one-slot kernel: the first
-// frames are dealt, and where those are all, no counter is needed (nor the
-// launch that clears it).  Every workgroup draws its second frame at the start,
-// so the counters are spread for those as well.
-void deal(Job &J, int grid) {
+// `rounds` frames of each workgroup are dealt (it holds one and knows the
+// next), and where those are all, no counter is needed (nor the launch that
+// clears it).  Two where all workgroups start at once: drawn, the second ones
+// come with an atomic of every workgroup, and most of a batch of little more
+// than `grid` finds every counter exhausted one by one (n = 108, rows of 9,
+// 4,000 frames: 0.059 ms with one dealt, 0.034 with two).  One where the launch
+// shares the GPU with others (the eight quasi-cyclic codes take 1 % longer
+// with two).
+void deal(Job &J, int grid, int rounds) {
     if (J.variant < kNumVariants) return;
-    J.dealt = std::min(grid, J.B);
+    J.grid = grid;
+    J.rounds = rounds;
+    J.dealt = (int32_t)std::min<int64_t>(rounds * (int64_t)grid, J.B);
     if (J.dealt == J.B) J.queue = nullptr;
-    else J.nq = queues_for(std::max(J.B - J.dealt, 4 * grid));
+    else J.nq = queues_for(std::max(J.B - J.dealt, 4 * grid)); // (every workgroup draws at about the same time)
 }
 
 // Grid of a persistent launch: every CU filled to its occupancy, but no more
@@ -336,7 +343,7 @@ int onchip_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, u
     JobTable jt{};
     jt.njobs = 1;
     Job &J = jt.job[0] = make_job(g, v, llr, B, bits, post, iters, ok, alpha, beta, (uint32_t *)ws);
-    deal(J, grid);
+    deal(J, grid, 2);
     if (J.queue) k_zero_words<<<(kQueueWords + 255) / 256, 256, 0, stream>>>(J.queue, kQueueWords);
     timed_launch(K_ONCHIP, fn, grid, threads, lds, stream, jt, L, early);
     return hipGetLastError() == hipSuccess ? LDPC_OK : LDPC_EHIP;
@@ -453,7 +460,6 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
                                        ? 1
                                        : 2 * kVariants[own[a].J.variant].f);
         if (st) return st;
-        if (ot.njobs == 1) deal(ot.job[0], grid);
         launches.push_back(Launch{own[a].fn, grid, t, l, ot});
     }
     if (frames > 0) {
@@ -467,6 +473,8 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
     // enqueued on `stream` so far and which `stream` waits for at the end.
     // Each launch's last frames (and the shared launch of small jobs) then
     // overlap the others instead of leaving CUs idle.
+    for (Launch &x : launches)
+        if (x.jt.njobs == 1) deal(x.jt.job[0], x.grid, launches.size() == 1 ? 2 : 1);
     SideStreams *side = launches.size() > 1 ? side_streams() : nullptr;
     std::unique_lock<std::mutex> hold;
     if (side) {

@@ -132,9 +132,9 @@ struct Job {
     const float *alpha, *beta; // learned weights (T x ncls) or null
     int32_t ncls;
     int32_t variant;  // index into kVariants
-    // One-slot kernels: frame k below `dealt` goes to workgroup k, the others are
-    // taken from the counters.
-    int32_t dealt;
+    // One-slot kernels: frame k below `dealt` goes to workgroup k modulo the grid
+    // (`rounds` of them to each), the others are taken from the counters.
+    int32_t dealt, grid, rounds;
     uint32_t *queue;  // kQueues frame counters (kQueueStride words apart), zero before the launch;
                       // null if every frame is dealt
     int32_t nq;       // counters in use (queues_for)
@@ -266,27 +266,23 @@ __device__ __forceinline__ void run_onchip(const Job &J, int32_t L, int32_t earl
     }
 
     // ---- slots --------------------------------------------------------------
-    // One slot: the first frames are dealt, and the counters (null if that is
-    // all) hand out the others.  (Elsewhere the five registers that this takes
-    // would cost the two-slot kernels a wave per SIMD.)
+    // One slot: the first frame or two of every workgroup are dealt, and the
+    // counters (null if that is all) hand out the others.  (Elsewhere the
+    // registers that this takes would cost the two-slot kernels a wave per SIMD.)
     constexpr bool kDeal = kLay && F == 1;
     const int32_t dealt = kDeal ? J.dealt : 0, left = B - dealt;
     if (tid == 0) {
-        // 2 F consecutive values of the home counter with one atomic (F, where
-        // the first F are dealt); any that fall past the end come from the
-        // other counters
+        // 2 F consecutive values of the home counter with one atomic; any that
+        // fall past the end come from the other counters
         int32_t hc = (int32_t)(blockIdx.x % (uint32_t)nq);
         uint32_t dead = 0u;
-        const int first = kDeal && dealt > 0 ? F : 0;
         int32_t fs[2 * F];
         if constexpr (kDeal) {
-#pragma unroll
-            for (int i = 0; i < F; ++i) {
-                fs[i] = (int32_t)blockIdx.x * F + i; // (overwritten unless dealt)
-                fs[F + i] = B;
-            }
+            fs[0] = (int32_t)blockIdx.x; // (both overwritten unless dealt)
+            fs[1] = min(J.grid + (int32_t)blockIdx.x, B);
         }
-        if (!kDeal || queue) {
+        const int first = kDeal ? J.rounds : 0; // frames dealt to the slot
+        if (!kDeal || (queue && first < 2)) {
             const uint32_t k0 = atomicAdd(queue + hc * kQueueStride, 2u * F - (uint32_t)first);
             const int32_t home = hc;
 #pragma unroll
@@ -297,10 +293,10 @@ __device__ __forceinline__ void run_onchip(const Job &J, int32_t L, int32_t earl
                     fs[i] = dealt + (int32_t)f;
                 } else {
                     if (!((dead >> home) & 1u)) {
-                        dead = mark_dead(queue, home, dead);
+                        dead = mark_dead<kDeal>(queue, home, dead);
                         hc = next_live(home, dead, nq);
                     }
-                    fs[i] = dealt + take_frame(queue, left, nq, hc, dead);
+                    fs[i] = dealt + take_frame<kDeal>(queue, left, nq, hc, dead);
                 }
             }
         }
@@ -552,7 +548,7 @@ __device__ __forceinline__ void run_onchip(const Job &J, int32_t L, int32_t earl
                 if (!kDeal || queue) {
                     int32_t hc = sh->hc;
                     uint32_t dead = sh->dead;
-                    nn = dealt + take_frame(queue, left, nq, hc, dead);
+                    nn = dealt + take_frame<kDeal>(queue, left, nq, hc, dead);
                     sh->hc = hc;
                     sh->dead = dead;
                 }

@@ -129,3 +129,27 @@ def test_regular_forms_leave_forced_paths_and_records_alone():
         ldpc.set_tuning(g, path=1, variant=variant)
         assert ldpc.get_tuning(g)["variant"] == variant
         assert all(torch.equal(a, b) for a, b in zip(ldpc.minsum_decode(g, x, 9), plain))
+
+
+@pytest.mark.parametrize("dv,dc,n,B", [(3, 6, 102, 9001), (3, 6, 102, 17003), (3, 9, 108, 5000), (4, 8, 2000, 1025),
+                                       (4, 8, 2000, 1300), (2, 5, 400, 4999), (2, 5, 400, 9001), (4, 20, 6000, 900)])
+def test_batches_of_a_few_frames_per_workgroup(dv, dc, n, B):
+    """Between one and three frames per resident workgroup, where the second
+    frames are dealt and the third ones drawn, many of them from counters that
+    run out at the same time: every frame is decoded once, as in small batches."""
+    import torch
+    from paper_2507_10424_amd import ldpc
+    dev = torch.device("cuda:0")
+    H = wl.regular_ldpc(n, n * dv // dc, dv, dc, seed=3)
+    g = ldpc.build_graph(torch.from_numpy(np.ascontiguousarray(H)).to(dev))
+    rate = 1 - dv / dc
+    note(f"[few] ({dv},{dc}) n={n} B={B}")
+    x = torch.from_numpy(wl.bpsk_awgn_llr(None, 2.5 + 5.5 * max(0.0, rate - 0.5), rate, seed=B, n=n, batch=B)).to(dev)
+    out = ldpc._outputs(B, n, dev, True)
+    for t, v in zip(out, (7, float("nan"), -7, 9)):
+        t.fill_(v)
+    ldpc.minsum_decode(g, x, 20, out=out)
+    for k in range(0, B, 250):
+        part = ldpc.minsum_decode(g, x[k:k + 250], 20)
+        for a, b in zip(out, part):
+            assert torch.equal(a[k:k + 250], b), k
