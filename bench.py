@@ -121,7 +121,7 @@ def parse():
     ap.add_argument("--no-autotune", action="store_true", help="skip the autotuner (library defaults)")
     ap.add_argument("--tuning", default=None,
                     help="set the tuning record instead of autotuning: path,variant,wg_per_cu,stream_waves,"
-                         "waves_per_simd[,stream_nt[,stream_chunk]] (as printed by a tuned run)")
+                         "waves_per_simd[,stream_nt[,stream_chunk[,idle]]] (as printed by a tuned run)")
     ap.add_argument("--path", default="auto", choices=["auto", "stream", "onchip"])
     ap.add_argument("--streams", type=int, default=0,
                     help="HIP streams the Eb/N0 batches are issued on (0: 3 on the on-chip path, else 1)")
@@ -140,7 +140,7 @@ def parse():
                     help="skip the decode from and to pinned host memory (PCIe-inclusive rate)")
     ap.add_argument("--profile-only", action="store_true", help="warmup + timed steps, no extras (for rocprofv3)")
     ap.add_argument("--multi-tuning", default=None,
-                    help="multi8: per code variant,waves_per_simd,wg_per_cu of the on-chip path, codes separated "
+                    help="multi8: per code variant,waves_per_simd,wg_per_cu[,idle] of the on-chip path, codes separated "
                          "by ';' (as printed by a tuned run), instead of autotuning each code")
     ap.add_argument("--copy-probe", action="store_true",
                     help="only copy 256 MiB three times (calibrates the HBM byte counters of a profiler)")
@@ -242,7 +242,8 @@ def main():
     if args.path != "auto":
         onchip = args.path == "onchip"
     else:
-        onchip = tuning["path"] == 1 if tuning else args.config != "qc64800"
+        in_force = tuning is not None and not tuning["idle"]
+        onchip = tuning["path"] == 1 if in_force else args.config != "qc64800"
     nstreams = args.streams if args.streams else (min(3, len(llrs)) if onchip else 1)
     side = [torch.cuda.Stream(device=dev) for _ in range(nstreams)] if nstreams > 1 else []
     side_ws = [ws] + [torch.empty_like(ws) for _ in range(nstreams - 1)]
@@ -390,7 +391,7 @@ def main():
     # Cache; the same step decoding the whole batch at once (every launch
     # streams all frames' state through HBM) is timed beside it.
     whole = None
-    if tuning is not None and tuning.get("path") == 2 and tuning.get("stream_chunk") != 0:
+    if tuning is not None and not tuning["idle"] and tuning["path"] == 2 and tuning["stream_chunk"] != 0:
         ref_out = [(o[0].clone(), o[2].clone()) for o in outs]
         ldpc.set_tuning(g, 2, stream_waves=tuning["stream_waves"], stream_nt=-1, stream_chunk=0)
         step()
@@ -913,15 +914,16 @@ def multi_measure(args, W, dev, lib, autotune=True, steps=None, warmup=None):
     fixed = None
     if getattr(args, "multi_tuning", None):
         fixed = [[int(x) for x in part.split(",")] for part in args.multi_tuning.split(";")]
-        if len(fixed) != len(fam) or any(len(f) != 3 for f in fixed):
-            raise SystemExit(f"--multi-tuning needs {len(fam)} entries of variant,waves_per_simd,wg_per_cu")
+        if len(fixed) != len(fam) or any(len(f) not in (3, 4) for f in fixed):
+            raise SystemExit(f"--multi-tuning needs {len(fam)} entries of variant,waves_per_simd,wg_per_cu[,idle]")
     for k, c in enumerate(fam):
         graphs.append(ldpc.build_graph(torch.from_numpy(c["H"]).to(dev)))
         llrs.append(wl.bpsk_awgn_llr_torch(None, W["ebn0"][0], c["rate"], W["seed_noise"] + k, dev, n=c["n"],
                                            batch=c["batch"]))
         if fixed:
-            v, wps, wpc = fixed[k]
-            ldpc.set_tuning(graphs[-1], 1, variant=v, waves_per_simd=wps, wg_per_cu=wpc)
+            v, wps, wpc = fixed[k][:3]
+            ldpc.set_tuning(graphs[-1], 1, variant=v, waves_per_simd=wps, wg_per_cu=wpc,
+                            idle=fixed[k][3] if len(fixed[k]) > 3 else 0)
             tunings.append(ldpc.get_tuning(graphs[-1]))
         elif autotune:  # each code's own launch choice, as for one code
             tunings.append(ldpc.autotune(graphs[-1], min(c["batch"], 65536), L, W["ebn0"][0]))

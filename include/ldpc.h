@@ -347,6 +347,7 @@ int ldpc_adam_step(float *param_dev, const float *grad_dev, float *m1_dev, float
  *                 four (three) resident waves per SIMD (fewer registers per
  *                 thread)
  *   ms            ldpc_autotune: mean time of one decode of the tuning batch
+ *                 with the launch that the record names
  *   stream_nt     streaming path: 1 marks the message loads and stores
  *                 non-temporal (they stream through the caches and leave them
  *                 to the posterior gathers), 0 not, -1 by size (non-temporal
@@ -357,8 +358,12 @@ int ldpc_adam_step(float *param_dev, const float *grad_dev, float *m1_dev, float
  *                 the launches; 0 all tiles at once, k > 0 k tiles, -1 by size
  *                 (as many tiles as fit 200 MiB of posteriors, channel LLRs
  *                 and messages, at least one)
+ *   idle          1: the record is kept and reported, but the graph decodes as
+ *                 if it had none (ldpc_autotune found that faster: the
+ *                 LDS-resident decoder, the one-slot kernels, which no record
+ *                 names); 0: the record is in force
  * LDPC_FORCE_STREAM / LDPC_FORCE_ONCHIP still override the path, and a record
- * that ldpc_graph_set_tuning set means the on-chip or streaming kernels.
+ * in force means the on-chip or streaming kernels.
  */
 typedef struct ldpc_tuning {
     int32_t path;
@@ -369,9 +374,12 @@ typedef struct ldpc_tuning {
     float ms;
     int32_t stream_nt;
     int32_t stream_chunk;
+    int32_t idle;
 } ldpc_tuning;
 
-/* Set (t != NULL) or clear (t == NULL) the tuning record.  Not thread-safe
+/* Set (t != NULL) or clear (t == NULL) the tuning record.  A record read with
+ * ldpc_graph_get_tuning or returned by ldpc_autotune, set again, has the graph
+ * decode as it did.  Not thread-safe
  * against concurrent decodes of the same graph.  Errors: LDPC_EINVAL,
  * LDPC_EUNSUPPORTED (the variant does not fit the graph). */
 int ldpc_graph_set_tuning(ldpc_graph *g, const ldpc_tuning *t);
@@ -391,8 +399,8 @@ int ldpc_graph_get_tuning(const ldpc_graph *g, ldpc_tuning *t);
  * of four decodes), and stores the fastest of those in the graph's tuning
  * record (also returned in *best if non-null).  Where decoding
  * without a record was faster still (the LDS-resident decoder, the one-slot
- * kernels), the fastest record is kept and reported, with the faster time in
- * best->ms, and the graph goes on decoding without it.
+ * kernels), the fastest record is kept and reported as idle, and the graph
+ * goes on decoding without it.
  * It synchronises `stream` and
  * creates two HIP events; do not capture it.  The workspace needs
  * ldpc_autotune_workspace_bytes(g, B) bytes.

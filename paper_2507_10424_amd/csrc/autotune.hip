@@ -73,10 +73,11 @@ extern "C" int ldpc_graph_set_tuning(ldpc_graph *g, const ldpc_tuning *t) {
     if (t->path == 2 && (t->stream_waves < 1 || t->stream_waves > 8)) return LDPC_EINVAL;
     if (t->stream_nt < -1 || t->stream_nt > 1) return LDPC_EINVAL;
     if (t->stream_chunk < -1) return LDPC_EINVAL;
+    if (t->idle != 0 && t->idle != 1) return LDPC_EINVAL;
     if (t->path == 1 && t->waves_per_simd != 0 && t->waves_per_simd != 3 && t->waves_per_simd != 4)
         return LDPC_EINVAL;
     g->tuning.set = true;
-    g->tuning.idle = false;
+    g->tuning.idle = t->idle == 1;
     g->tuning.path = t->path;
     g->tuning.variant = t->variant;
     g->tuning.wg_per_cu = t->wg_per_cu;
@@ -97,6 +98,7 @@ extern "C" int ldpc_graph_get_tuning(const ldpc_graph *g, ldpc_tuning *t) {
     t->stream_chunk = g->tuning.stream_chunk;
     t->waves_per_simd = g->tuning.waves_per_simd;
     t->ms = 0.0f;
+    t->idle = g->tuning.set && g->tuning.idle ? 1 : 0;
     return LDPC_OK;
 }
 
@@ -140,7 +142,7 @@ extern "C" int ldpc_autotune(ldpc_graph *g, int32_t B, int32_t max_iter, float e
             if (wps != 0 && onchip_kernel_spill_bytes(v, wps) > 320) continue;
             if (wps == 4 && regs >= 0 && regs <= 128) continue;
             if (wps == 3 && regs >= 0 && regs <= 168) continue;
-            for (int wpc : {0, 1, 2, 3, 4}) cands.push_back(ldpc_tuning{1, v, wpc, 4, wps, 0.0f, -1, -1});
+            for (int wpc : {0, 1, 2, 3, 4}) cands.push_back(ldpc_tuning{1, v, wpc, 4, wps, 0.0f, -1, -1, 0});
         }
     }
     // Chunked streaming only where the size rule splits this batch.
@@ -148,7 +150,7 @@ extern "C" int ldpc_autotune(ldpc_graph *g, int32_t B, int32_t max_iter, float e
     for (int chunk : {0, -1}) {
         if (chunk == -1 && !chunks) continue;
         for (int nt : {0, 1})
-            for (int waves : {1, 2, 4, 8}) cands.push_back(ldpc_tuning{2, -1, 0, waves, 0, 0.0f, nt, chunk});
+            for (int waves : {1, 2, 4, 8}) cands.push_back(ldpc_tuning{2, -1, 0, waves, 0, 0.0f, nt, chunk, 0});
     }
 
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -205,7 +207,6 @@ extern "C" int ldpc_autotune(ldpc_graph *g, int32_t B, int32_t max_iter, float e
     // Decoding without a record can be faster still (the LDS-resident decoder,
     // the one-slot kernels, which no record names): then the fastest record is
     // kept, but lies idle.
-    bool idle = false;
     if (st == LDPC_OK && best_k >= 0 && (onchip_fits(*g) || lds_fits(*g))) {
         g->tuning.set = false;
         auto run = [&]() {
@@ -219,10 +220,7 @@ extern "C" int ldpc_autotune(ldpc_graph *g, int32_t B, int32_t max_iter, float e
         if (st == LDPC_OK && (hipEventRecord(e1, stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                               hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
             st = LDPC_EHIP;
-        if (st == LDPC_OK && ms / 4 < 0.97f * cands[best_k].ms) { // (by more than the runs differ)
-            idle = true;
-            cands[best_k].ms = ms / 4;
-        }
+        if (st == LDPC_OK && ms / 4 < 0.97f * cands[best_k].ms) cands[best_k].idle = 1; // (by more than the runs differ)
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
@@ -231,7 +229,6 @@ extern "C" int ldpc_autotune(ldpc_graph *g, int32_t B, int32_t max_iter, float e
         return st ? st : LDPC_EHIP;
     }
     st = ldpc_graph_set_tuning(g, &cands[best_k]);
-    g->tuning.idle = idle;
     if (best) *best = cands[best_k];
     return st;
 }
