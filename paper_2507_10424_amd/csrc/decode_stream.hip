@@ -905,7 +905,7 @@ int stream_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, u
     const int32_t frames = nt * kTile;
     const int32_t period = test_period(flags); // 0: no early exit
     // wavefronts per workgroup of the check / bit kernels (tuning record, else 4)
-    const int32_t waves = (g.tuning.set && g.tuning.stream_waves > 0) ? g.tuning.stream_waves : 4;
+    const int32_t waves = (g.tuned() && g.tuning.stream_waves > 0) ? g.tuning.stream_waves : 4;
     const int32_t row_blocks = (g.m + waves - 1) / waves;                     // one row per wavefront
     const int32_t row_blocks_dc = (g.m + waves * kRowsPerWave - 1) / (waves * kRowsPerWave);
     const int32_t col_blocks = (g.n + waves * kColsPerWave - 1) / (waves * kColsPerWave);
@@ -919,7 +919,7 @@ int stream_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, u
     // by every launch after its first.  Each frame sees the same launches in
     // the same order as without chunks; only frames of different chunks are
     // interleaved differently.
-    const bool tuned = g.tuning.set && g.tuning.path == 2;
+    const bool tuned = g.tuned() && g.tuning.path == 2;
     const int32_t chunk = stream_chunk_tiles(g, B, tuned ? g.tuning.stream_chunk : -1);
     // Non-temporal message accesses: the tuning record's choice, else when one
     // iteration's messages of a chunk (4 E bytes per frame) exceed 2 GiB and

@@ -59,3 +59,17 @@ def test_idle_record_survives_get_and_set():
     assert e.value.status == -1
     ldpc.set_tuning(g, None)
     assert ldpc.get_tuning(g)["path"] == 0 and ldpc.get_tuning(g)["idle"] == 0
+
+
+def test_forced_streaming_leaves_an_idle_record_out():
+    torch, ldpc, Hd, llr = setup(130)  # three tiles
+    g = ldpc.build_graph(Hd)
+    flags = ldpc.LDPC_FORCE_STREAM | ldpc.LDPC_NO_EARLY_EXIT
+    run = lambda: ldpc.minsum_decode(g, llr, 4, flags=flags)  # noqa: E731
+    ref, none = launches(torch, ldpc, run)
+    assert none == [4, 0]  # all tiles in one chunk
+    for idle, want in ((1, [4, 0]), (0, [12, 0])):  # one tile to a chunk only where the record is in force
+        ldpc.set_tuning(g, 2, stream_chunk=1, idle=idle)
+        out, counts = launches(torch, ldpc, run)
+        assert counts == want, (idle, counts)
+        assert all(torch.equal(a, b) for a, b in zip(ref, out))
