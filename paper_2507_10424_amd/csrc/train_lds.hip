@@ -6,8 +6,8 @@
 //
 // Bound (n = 1024, (3,6)): VALU.  Forward: 33 instructions per row and
 // iteration for the check update, about 20 for the record, 3 per bit, and the
-// softplus of every posterior (25); backward: about 10 per edge and the sigmoid
-// (17) per bit.  Memory: 10 KB per frame and iteration written, then read
+// softplus of every posterior (38); backward: about 10 per edge and the sigmoid
+// (29) per bit.  Memory: 10 KB per frame and iteration written, then read
 // (2.8 and 2.1 TB/s in the two kernels, 0.151 and 0.204 ms for 4,096 frames).
 #include <algorithm>
 
