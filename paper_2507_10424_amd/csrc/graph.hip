@@ -365,7 +365,7 @@ int build(const uint8_t *H, int32_t m, int32_t n, hipStream_t s, ldpc_graph *g) 
                     return fail(LDPC_EHIP);
                 return (int)LDPC_OK;
             };
-            if (ldpc::lds_tables(h_rowptr, h_bit, h_class, m, n, &T)) {
+            if (ldpc::lds_tables(h_rowptr, h_bit, h_class, m, n, &T, (size_t)g->lds_max)) {
                 G.lds.row_groups = (int32_t)T.row_group.size();
                 G.lds.bit_groups = (int32_t)T.bit_group.size();
                 G.lds.npos = T.npos;

@@ -173,12 +173,14 @@ bool onchip_cf_geometry(const ldpc_graph &g, const std::vector<int32_t> &col_deg
                         int32_t *dvs, uint32_t *dvp);
 
 // LDS-resident decoder for other codes whose state fits one CU: its tables
-// (false if the graph is out of its range), whether it takes the graph, launch
-// (of the workspace, whichever path's, it uses the first 2,176 bytes).
+// (false if the graph is out of its range or its state takes more than lds_max
+// bytes), whether it takes the graph, launch (of the workspace, whichever
+// path's, it uses the first 2,176 bytes).
 constexpr int kLdsMaxThreads = 1024; // of a workgroup
 constexpr int kLdsMaxDegree = 32;    // of a row
 bool lds_tables(const std::vector<int32_t> &rowptr, const std::vector<int32_t> &col,
-                const std::vector<int32_t> &row_class, int32_t m, int32_t n, LdsHostTables *out);
+                const std::vector<int32_t> &row_class, int32_t m, int32_t n, LdsHostTables *out,
+                size_t lds_max = SIZE_MAX);
 bool lds_fits(const ldpc_graph &g);
 int lds_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, uint32_t flags, const float *alpha,
                const float *beta, uint8_t *bits, float *post, int32_t *iters, uint8_t *ok, void *ws,

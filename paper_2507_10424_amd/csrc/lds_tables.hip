@@ -43,15 +43,21 @@ void spread_banks(const std::vector<int32_t> &rowptr, const std::vector<int32_t>
         for (int32_t e = rowptr[i]; e < rowptr[i + 1]; ++e)
             use[fill[col[e]]++] = Use{(int32_t)(((size_t)place[i] / 32 * kLdsMaxDegree + (e - rowptr[i])) * kBanks),
                                       place[i] % kBanks};
-    int32_t dv = 0;
-    for (int32_t j = 0; j < n; ++j) dv = std::max(dv, colptr[j + 1] - colptr[j]);
-    std::vector<int16_t> rh(halves * kLdsMaxDegree * kBanks, 0);               // check pass
-    std::vector<int16_t> bh((size_t)((n + 31) / 32) * std::max(dv, 1) * kBanks, 0); // bit pass
+    std::vector<int16_t> rh(halves * kLdsMaxDegree * kBanks, 0); // check pass
+    // bit pass: bins for the largest degree of each half (its first slot's), so that one long column costs its
+    // own half only
+    std::vector<size_t> bit_half((size_t)(n + 31) / 32);
+    size_t bins = 0;
+    for (size_t h = 0; h < bit_half.size(); ++h) {
+        bit_half[h] = bins;
+        bins += (size_t)(colptr[bits[32 * h] + 1] - colptr[bits[32 * h]]) * kBanks;
+    }
+    std::vector<int16_t> bh(bins, 0);
     auto put = [&](int32_t j, int32_t p, int s) { // adds (takes) bit j at slot p; the change of the sums
         int32_t d = 0;
         for (int32_t q = colptr[j]; q < colptr[j + 1]; ++q) {
             int16_t &a = rh[(size_t)use[q].hist + p % kBanks];
-            int16_t &b = bh[((size_t)(p / 32) * dv + (q - colptr[j])) * kBanks + use[q].lane];
+            int16_t &b = bh[bit_half[p / 32] + (size_t)(q - colptr[j]) * kBanks + use[q].lane];
             d += 2 * s * (a + b) + 2;
             a += (int16_t)s;
             b += (int16_t)s;
@@ -90,7 +96,7 @@ void spread_banks(const std::vector<int32_t> &rowptr, const std::vector<int32_t>
 } // namespace
 
 bool lds_tables(const std::vector<int32_t> &rowptr, const std::vector<int32_t> &col,
-                const std::vector<int32_t> &row_class, int32_t m, int32_t n, LdsHostTables *out) {
+                const std::vector<int32_t> &row_class, int32_t m, int32_t n, LdsHostTables *out, size_t lds_max) {
     std::vector<int32_t> rows, colptr(n + 1, 0);
     int32_t dmax = 0;
     for (int32_t i = 0; i < m; ++i) {
@@ -101,6 +107,11 @@ bool lds_tables(const std::vector<int32_t> &rowptr, const std::vector<int32_t> &
     if (dmax > kLdsMaxDegree || n > 16 * kLdsMaxThreads || rows.empty()) return false;
     auto deg = [&](int32_t i) { return rowptr[i + 1] - rowptr[i]; };
     std::stable_sort(rows.begin(), rows.end(), [&](int32_t a, int32_t b) { return deg(a) > deg(b); });
+    // The message positions, and whether a frame's state fits at all (n = 15000, rows of up to 16, which does not: a
+    // graph build of 30 ms with the search below, 5 without).
+    size_t positions = 0;
+    for (size_t p = 0; p < rows.size(); p += 64) positions += 64 * (size_t)row_bucket(deg(rows[p]));
+    if (positions + 1 > 65535 || 4 * ((size_t)n + positions + 2) > lds_max) return false;
     for (int32_t j : col) ++colptr[j + 1];
     std::partial_sum(colptr.begin(), colptr.end(), colptr.begin());
     std::vector<int32_t> bits(n);
@@ -139,7 +150,6 @@ bool lds_tables(const std::vector<int32_t> &rowptr, const std::vector<int32_t> &
         T.npos += 64 * G.degree;
         T.row_group.push_back(G);
     }
-    if (T.npos + 1 > 65535) return false;
     T.rows.resize(T.rows.size() + kLdsMaxDegree / 2 * 64, 0u); // read, but not used, past the last group
     std::vector<int32_t> fill(colptr.begin(), colptr.end() - 1), csc(col.size());
     for (size_t e = 0; e < col.size(); ++e) csc[fill[col[e]]++] = (int32_t)e; // ascending row in every column
