@@ -265,8 +265,10 @@ __device__ __forceinline__ uint32_t check_row(const int32_t *__restrict__ ci, co
 // being computed (1-based).  Rows of 2 to 16, 20, 24, 28 and 32 edges are
 // unrolled, one scalar branch away (a loop keeps one posterior and one message
 // in flight: irregular n = 15000, 2,000 frames, 11.6 -> 6.5 ms; (4,8) n = 16000
-// 13.3 -> 9.4 ms); others take the loop at the end.
-template <bool NT>
+// 13.3 -> 9.4 ms); others take the loop at the end.  MAXD: longest row that is
+// unrolled, 16 or 32 (its registers, 49 or 89, are every wavefront's and leave 8
+// or 5 waves per SIMD).
+template <int MAXD, bool NT>
 __global__ __launch_bounds__(512) void k_check(const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col_idx,
                                                const int32_t *__restrict__ row_class, int32_t m, int32_t n, int64_t E,
                                                int32_t row_blocks, const Bufs bufs, int32_t t,
@@ -304,7 +306,10 @@ __global__ __launch_bounds__(512) void k_check(const int32_t *__restrict__ row_p
         switch (e1 - e0) {
 #define LDPC_ROW(D)                                                                                                  \
     case D:                                                                                                          \
-        syn = check_row<D, NT>(col_idx + e0, sv, et + (size_t)e0 * kTile, t == 1, alpha != nullptr, al, be);         \
+        if constexpr (D <= MAXD)                                                                                     \
+            syn = check_row<D, NT>(col_idx + e0, sv, et + (size_t)e0 * kTile, t == 1, alpha != nullptr, al, be);     \
+        else                                                                                                         \
+            loop = true;                                                                                             \
         break;
             LDPC_ROW(2) LDPC_ROW(3) LDPC_ROW(4) LDPC_ROW(5) LDPC_ROW(6) LDPC_ROW(7) LDPC_ROW(8) LDPC_ROW(9)
             LDPC_ROW(10) LDPC_ROW(11) LDPC_ROW(12) LDPC_ROW(13) LDPC_ROW(14) LDPC_ROW(15) LDPC_ROW(16) LDPC_ROW(20)
@@ -913,6 +918,11 @@ int stream_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, u
     const int32_t ncls = (int32_t)g.class_degrees.size();
     // unrolled check kernel when every row has 6 or 7 edges
     const int32_t regular = (g.dc_min == g.dc_max && (g.dc_max == 6 || g.dc_max == 7)) ? g.dc_max : 0;
+    // else the form with rows of up to 32 only where all rows above 16 are
+    // unrolled in it: the loop, bound by latency, wants the waves ((4,40) n =
+    // 20000, 2,000 frames: 5.49 ms in that form, 4.71 in the other)
+    bool long_rows = g.dc_max > 16;
+    for (int32_t d : g.class_degrees) long_rows = long_rows && (d <= 16 || (d <= 32 && d % 4 == 0));
 
     // Chunks: all L iterations of `chunk` tiles before the next tiles, so that
     // a chunk that fits the Infinity Cache is read from there, not from HBM,
@@ -964,7 +974,7 @@ int stream_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, u
                 timed_launch(K_CHECK, fn, ct * row_blocks_dc, 64 * waves, 0, stream, cidx, rcls, g.m, g.n, g.E,
                              row_blocks_dc, b, t, alpha, beta, ncls);
             } else
-                timed_launch(K_CHECK, k_check<NT>, ct * row_blocks, 64 * waves, 0, stream, g.row_ptr, g.col_idx,
+                timed_launch(K_CHECK, long_rows ? k_check<32, NT> : k_check<16, NT>, ct * row_blocks, 64 * waves, 0, stream, g.row_ptr, g.col_idx,
                              g.row_class, g.m, g.n, g.E, row_blocks, b, t, alpha, beta, ncls);
             // is the decision of iteration t - 1 tested?
             const int32_t test_now = (period > 0 && (t - 1) % period == 0) ? 1 : 0;
