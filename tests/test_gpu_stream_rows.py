@@ -49,3 +49,22 @@ def test_row_degrees(name, learned):
             ref = oracle_decode(H, llr, L, flags)
         torch.cuda.synchronize()
         assert_parity(tuple(t.cpu().numpy() for t in out), ref, f"{name} flags {flags}")
+
+
+@pytest.mark.parametrize("B", [1, 15, 16, 17, 33, 64, 81])
+@pytest.mark.parametrize("code", ["regular", "mixed"])
+def test_partial_rows(code, B):
+    """The last tile's frames end at any lane, and frames stop lane by lane."""
+    import torch
+    from paper_2507_10424_amd import ldpc
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dev = torch.device("cuda:0")
+    H = (wl.regular_ldpc(120, 60, 3, 6, seed=2) if code == "regular" else
+         wl.random_irregular_code(130, 60, seed=3, dv_choices=(2, 3, 4), max_row_degree=12))
+    n, L = H.shape[1], 20
+    llr = wl.bpsk_awgn_llr(None, 2.5, 0.5, seed=20 + B, n=n, batch=B)
+    g = ldpc.build_graph(torch.from_numpy(H).to(dev))
+    out = ldpc.minsum_decode(g, torch.from_numpy(llr).to(dev), L, flags=ldpc.LDPC_FORCE_STREAM)
+    torch.cuda.synchronize()
+    assert_parity(tuple(t.cpu().numpy() for t in out), oracle_decode(H, llr, L), f"{code} B={B}")
