@@ -751,11 +751,12 @@ constexpr int kMoveRows = 128; // rows of r, s and eta per wavefront of the copy
 // phases: the packed tiles are the first ones of the batch.
 __global__ __launch_bounds__(kPlanThreads) void k_compact_plan(const Bufs bufs, int32_t ct, int32_t remaining,
                                                                int32_t phases, int32_t *__restrict__ base) {
-    __shared__ int32_t part[kPlanThreads], tiles_on[kPlanThreads];
+    __shared__ int32_t part[kPlanThreads], tiles_on[kPlanThreads], last;
     // the frames are where the previous plan left them (copied if it went ahead)
     const uint32_t c = __builtin_amdgcn_readfirstlane(bufs.ctrl->cur ^ bufs.ctrl->go);
     const Set S = c ? bufs.set[1] : bufs.set[0];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, nw = kPlanThreads / 64;
+    if (tid == 0) last = 0;
     for (int32_t tile = w; tile < ct; tile += nw) {
         const uint64_t on = __ballot(S.done[tile * kTile + lane] == 0u);
         if (lane == 0) base[tile] = __popcll(on);
@@ -768,6 +769,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_compact_plan(const Bufs bufs, 
     for (int32_t k = a0; k < a1; ++k) {
         sum += base[k];
         on += base[k] > 0;
+        if (base[k] > 0) atomicMax(&last, k + 1);
     }
     part[tid] = sum;
     tiles_on[tid] = on;
@@ -796,7 +798,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_compact_plan(const Bufs bufs, 
         // the tiles saved over the iterations left repay that twice
         const bool go = t_on - packed >= 1 && (int64_t)(t_on - packed) * remaining >= (int64_t)(t_on + packed);
         bufs.ctrl->go = go ? 1u : 0u;
-        if (phases && go) bufs.ctrl->tiles = packed;
+        if (phases) bufs.ctrl->tiles = go ? packed : last;
     }
 }
 
