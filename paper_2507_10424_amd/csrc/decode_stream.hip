@@ -79,17 +79,14 @@ __device__ __forceinline__ Set cur_set(const Bufs &b) {
     const Set s0 = b.set[0], s1 = b.set[1];
     return c ? s1 : s0;
 }
-// The set the last plan counted (the source of its copy).
-__device__ __forceinline__ Set plan_set(const Bufs &b) {
-    const uint32_t c = __builtin_amdgcn_readfirstlane(b.ctrl->cur);
-    const Set s0 = b.set[0], s1 = b.set[1];
-    return c ? s1 : s0;
-}
 
 // Workgroups that have work in a launch of `per_tile` workgroups for each tile of
-// a chunk: those of its tiles that still hold frames.  (Dealing the XCDs a
-// contiguous range of these alone keeps all of them busy when one tile of two
-// is left: check and bit kernel of n = 64800 @@XCD@@.)
+// a chunk: those of its tiles that still hold frames.  The XCDs are dealt a
+// contiguous range of these alone, which keeps all of them busy when one tile
+// of two is left.  (n = 64800, 200 frames at 1.6 dB, in phases: every workgroup
+// looks at its frames' flags 6.44 ms, those of ended tiles leave at once but the
+// ranges are the launch's 6.22, this 5.82; (3,6) n = 24000, 960 frames at 2 dB:
+// 6.23, 5.74 and 4.63.)
 __device__ __forceinline__ uint32_t busy_blocks(const Bufs &b, int32_t per_tile) {
     if (b.tile0 < 0) return gridDim.x; // (without a load that every other one would wait for)
     const int32_t left = __builtin_amdgcn_readfirstlane(b.ctrl->tiles) - b.tile0;
@@ -651,45 +648,48 @@ __global__ void k_out_flags(const Bufs bufs, int32_t slots, int32_t L, int32_t u
 // iterations and convergence flags too; else, after the last iteration,
 // every frame still in a slot.
 template <bool STOPPED>
+__device__ __forceinline__ void out_item(const Set &S, float (*t)[kTile + 1], int32_t item, int32_t n, int32_t L,
+                                         float *__restrict__ post, uint8_t *__restrict__ bits,
+                                         int32_t *__restrict__ iters, uint8_t *__restrict__ ok) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int32_t nchunks = (n + 63) / 64;
+    const int32_t tile = item / nchunks, j0 = (item % nchunks) * 64;
+    const int32_t f_lane = tile * kTile + lane;
+    const int32_t id_lane = S.fid[f_lane];
+    const bool emit = id_lane >= 0 && (!STOPPED || S.done[f_lane]);
+    if (!__syncthreads_or(emit)) return;
+    if (STOPPED && j0 == 0 && w == 0 && emit) { // a stopped frame: it stopped by the codeword test
+        iters[id_lane] = S.conv[f_lane];
+        if (ok) ok[id_lane] = 1;
+    }
+    const bool use_r = L == 0 || S.conv[f_lane] == 0;
+    const float *src = (use_r ? S.r : S.s) + (size_t)tile * n * kTile;
+#pragma unroll 4
+    for (int k = w; k < kTile; k += kWaves) {
+        const int32_t j = j0 + k;
+        t[lane][k] = (j < n) ? src[(size_t)j * kTile + lane] : 0.0f;
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int k = w; k < kTile; k += kWaves) {
+        const int32_t fk = tile * kTile + k;
+        const int64_t id = S.fid[fk];
+        const int32_t j = j0 + lane;
+        if (id >= 0 && (!STOPPED || S.done[fk]) && j < n) {
+            const float v = t[k][lane];
+            if (post) post[id * n + j] = v;
+            bits[id * n + j] = v < 0.0f ? 1 : 0;
+        }
+    }
+    __syncthreads(); // t is rewritten by the next item
+}
 __global__ __launch_bounds__(256) void k_out_tiles(const Bufs bufs, int32_t n, int32_t L, int32_t items,
                                                    float *__restrict__ post, uint8_t *__restrict__ bits,
                                                    int32_t *__restrict__ iters, uint8_t *__restrict__ ok) {
-    if (STOPPED && !bufs.ctrl->go) return;
-    const Set S = STOPPED ? plan_set(bufs) : cur_set(bufs);
+    const Set S = cur_set(bufs);
     __shared__ float t[kTile][kTile + 1];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int32_t nchunks = (n + 63) / 64;
-    for (int32_t item = blockIdx.x; item < items; item += gridDim.x) { // (tile, 64 bits)
-        const int32_t tile = item / nchunks, j0 = (item % nchunks) * 64;
-        const int32_t f_lane = tile * kTile + lane;
-        const int32_t id_lane = S.fid[f_lane];
-        const bool emit = id_lane >= 0 && (!STOPPED || S.done[f_lane]);
-        if (!__syncthreads_or(emit)) continue;
-        if (STOPPED && j0 == 0 && w == 0 && emit) { // a stopped frame: it stopped by the codeword test
-            iters[id_lane] = S.conv[f_lane];
-            if (ok) ok[id_lane] = 1;
-        }
-        const bool use_r = L == 0 || S.conv[f_lane] == 0;
-        const float *src = (use_r ? S.r : S.s) + (size_t)tile * n * kTile;
-#pragma unroll 4
-        for (int k = w; k < kTile; k += kWaves) {
-            const int32_t j = j0 + k;
-            t[lane][k] = (j < n) ? src[(size_t)j * kTile + lane] : 0.0f;
-        }
-        __syncthreads();
-#pragma unroll 4
-        for (int k = w; k < kTile; k += kWaves) {
-            const int32_t fk = tile * kTile + k;
-            const int64_t id = S.fid[fk];
-            const int32_t j = j0 + lane;
-            if (id >= 0 && (!STOPPED || S.done[fk]) && j < n) {
-                const float v = t[k][lane];
-                if (post) post[id * n + j] = v;
-                bits[id * n + j] = v < 0.0f ? 1 : 0;
-            }
-        }
-        __syncthreads(); // t is rewritten by the next item
-    }
+    for (int32_t item = blockIdx.x; item < items; item += gridDim.x) // (tile, 64 bits)
+        out_item<false>(S, t, item, n, L, post, bits, iters, ok);
 }
 
 // Dense decoder outputs (frame f in slot f): iterations and convergence flag.
@@ -757,12 +757,48 @@ __global__ __launch_bounds__(kPlanThreads) void k_compact_plan(const Bufs bufs, 
     const Set S = c ? bufs.set[1] : bufs.set[0];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, nw = kPlanThreads / 64;
     if (tid == 0) last = 0;
+    if (phases) { // the tiles past these hold no frames
+        ct = min(ct, __builtin_amdgcn_readfirstlane(bufs.ctrl->tiles));
+        if (ct == 0) {
+            if (tid == 0) {
+                bufs.ctrl->cur = c;
+                bufs.ctrl->go = 0u;
+                bufs.ctrl->active = 0;
+            }
+            return;
+        }
+    }
     for (int32_t tile = w; tile < ct; tile += nw) {
         const uint64_t on = __ballot(S.done[tile * kTile + lane] == 0u);
         if (lane == 0) base[tile] = __popcll(on);
     }
+    auto decide = [&](int32_t active, int32_t t_on, int32_t end) { // end: past the last tile with frames
+        const int32_t packed = (active + kTile - 1) / kTile;
+        bufs.ctrl->cur = c;
+        bufs.ctrl->active = active;
+        // the copy reads the running tiles and writes the packed ones, about
+        // 0.4 of an iteration's bytes per tile for rate-1/2 codes: go when
+        // the tiles saved over the iterations left repay that twice
+        const bool go = t_on - packed >= 1 && (int64_t)(t_on - packed) * remaining >= (int64_t)(t_on + packed);
+        bufs.ctrl->go = go ? 1u : 0u;
+        if (phases) bufs.ctrl->tiles = go ? packed : end;
+    };
     __syncthreads();
-    // exclusive scan of the per-tile counts: a contiguous segment per thread
+    if (ct <= 64) { // exclusive scan of the per-tile counts in one wavefront
+        if (w != 0) return;
+        const int32_t own = lane < ct ? base[lane] : 0;
+        int32_t sum = own;
+        for (int d = 1; d < 64; d <<= 1) {
+            const int32_t x = __shfl_up(sum, d, 64);
+            if (lane >= d) sum += x;
+        }
+        if (lane < ct) base[lane] = sum - own;
+        const uint64_t on = __ballot(own > 0);
+        const int32_t active = __shfl(sum, 63, 64);
+        if (lane == 0) decide(active, __popcll(on), on ? 64 - __clzll(on) : 0);
+        return;
+    }
+    // the same for more tiles: a contiguous segment per thread
     const int32_t per = (ct + kPlanThreads - 1) / kPlanThreads;
     const int32_t a0 = tid * per, a1 = a0 + per < ct ? a0 + per : ct;
     int32_t sum = 0, on = 0;
@@ -788,18 +824,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_compact_plan(const Bufs bufs, 
         base[k] = run;
         run += c;
     }
-    if (tid == 0) {
-        const int32_t active = part[kPlanThreads - 1], t_on = tiles_on[kPlanThreads - 1];
-        const int32_t packed = (active + kTile - 1) / kTile;
-        bufs.ctrl->cur = c;
-        bufs.ctrl->active = active;
-        // the copy reads the running tiles and writes the packed ones, about
-        // 0.4 of an iteration's bytes per tile for rate-1/2 codes: go when
-        // the tiles saved over the iterations left repay that twice
-        const bool go = t_on - packed >= 1 && (int64_t)(t_on - packed) * remaining >= (int64_t)(t_on + packed);
-        bufs.ctrl->go = go ? 1u : 0u;
-        if (phases) bufs.ctrl->tiles = go ? packed : last;
-    }
+    if (tid == 0) decide(part[kPlanThreads - 1], tiles_on[kPlanThreads - 1], last);
 }
 
 // Packed tile k goes to tile spread(k): consecutive packed tiles land in
@@ -815,22 +840,30 @@ __device__ __forceinline__ int32_t unspread(int32_t p, int32_t ct) {
     return p < 8 * stride ? (p % stride) * 8 + p / stride : p;
 }
 
-// Items 0 .. ct * blocks_per_tile - 1 copy the frames still decoding (one
-// source tile per blocks_per_tile items); the items after them mark the
-// destination slots past the packed frames empty.  A grid of at most a few
-// thousand workgroups walks the items, so a plan that does not go ahead
-// costs only that grid's launch.
-__global__ __launch_bounds__(256) void k_compact_move(const Bufs bufs, const int32_t *__restrict__ base, int32_t n,
-                                                      int64_t E, int32_t ct, int32_t spread_ct, int32_t blocks_per_tile,
-                                                      int32_t items) {
+// Where the plan goes ahead.  The first out_items items write the outputs of
+// the frames that have stopped; the next ct * blocks_per_tile copy the frames
+// still decoding (one source tile per blocks_per_tile items); the items after
+// them mark the destination slots past the packed frames empty.  A grid of at
+// most a few thousand workgroups walks the items, so a plan that does not go
+// ahead costs only that grid's launch.
+__global__ __launch_bounds__(256) void k_compact(const Bufs bufs, const int32_t *__restrict__ base, int32_t n,
+                                                 int64_t E, int32_t ct, int32_t spread_ct, int32_t blocks_per_tile,
+                                                 int32_t out_items, int32_t items, int32_t L,
+                                                 float *__restrict__ post, uint8_t *__restrict__ bits,
+                                                 int32_t *__restrict__ iters, uint8_t *__restrict__ ok) {
     if (!bufs.ctrl->go) return;
     const uint32_t c = __builtin_amdgcn_readfirstlane(bufs.ctrl->cur);
     const Set src = c ? bufs.set[1] : bufs.set[0];
     const Set dst = c ? bufs.set[0] : bufs.set[1];
+    __shared__ float t[kTile][kTile + 1];
     const int32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int32_t active = bufs.ctrl->active;
-    for (int32_t item = blockIdx.x; item < items; item += gridDim.x) {
+    for (int32_t item = blockIdx.x; item < items + out_items; item += gridDim.x) {
+        if (item >= items) {
+            out_item<true>(src, t, item - items, n, L, post, bits, iters, ok);
+            continue;
+        }
         if (item >= ct * blocks_per_tile) {
             const int32_t p = (item - ct * blocks_per_tile) * (int32_t)blockDim.x + threadIdx.x;
             if (p < ct * kTile && unspread(p / kTile, spread_ct) * kTile + p % kTile >= active) {
@@ -864,10 +897,15 @@ __global__ __launch_bounds__(256) void k_compact_move(const Bufs bufs, const int
         auto copy = [&](const float *a, float *d, int64_t rows_per_tile, int64_t lo, int64_t hi) {
             const float *ap = a + (size_t)tile * rows_per_tile * kTile + lane;
             float *dp = d + (size_t)dt * rows_per_tile * kTile + dl;
-#pragma unroll 8
-            for (int64_t q = lo; q < hi; ++q) {
-                const float v = ap[(size_t)q * kTile];
-                if (act) dp[(size_t)q * kTile] = v;
+            for (int64_t q = lo; q < hi; q += 8) { // eight rows in flight
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = ap[(size_t)(q + u < hi ? q + u : lo) * kTile];
+                if (act) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (q + u < hi) dp[(size_t)(q + u) * kTile] = v[u];
+                }
             }
         };
         if (q0 < n) copy(src.r, dst.r, n, q0, q1 < n ? q1 : n);
@@ -881,7 +919,7 @@ __global__ __launch_bounds__(256) void k_compact_move(const Bufs bufs, const int
 // Iterations after which a compaction is planned within a chunk (roughly
 // geometric: frames stop early at high Eb/N0 and late at low).
 constexpr int32_t kCompactAt[] = {4, 6, 8, 11, 15, 20, 26, 32, 37, 42, 46};
-constexpr int32_t kCompactGrid = 2048; // workgroups of the output and copy kernels of a plan
+constexpr int32_t kCompactGrid = 2048; // workgroups of the kernel after a plan
 constexpr int32_t kCompactMinTiles = 16; // chunks of fewer tiles are not compacted by themselves
 // Batches in chunks of fewer tiles are decoded in phases instead: every chunk
 // runs the iterations of a phase, then the frames of all chunks still decoding
@@ -962,10 +1000,9 @@ int stream_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, u
         const int32_t out_items = ct * nchunks;
         const int32_t move_items = ct * move_blocks + (ct * kTile + 255) / 256;
         k_compact_plan<<<1, kPlanThreads, 0, stream>>>(b, ct, remaining, spread_ct == 0 ? 1 : 0, w.base);
-        k_out_tiles<true><<<out_items < kCompactGrid ? out_items : kCompactGrid, 256, 0, stream>>>(
-            b, g.n, L, out_items, post, bits, iters, ok);
-        k_compact_move<<<move_items < kCompactGrid ? move_items : kCompactGrid, 256, 0, stream>>>(
-            b, w.base, g.n, g.E, ct, spread_ct, move_blocks, move_items);
+        const int32_t items = out_items + move_items;
+        k_compact<<<items < kCompactGrid ? items : kCompactGrid, 256, 0, stream>>>(
+            b, w.base, g.n, g.E, ct, spread_ct, move_blocks, out_items, move_items, L, post, bits, iters, ok);
     };
     // The last decisions of the ct tiles of b, then their outputs.
     auto finish = [&](const Bufs &b, int32_t ct) {
@@ -973,7 +1010,7 @@ int stream_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, u
         k_syndrome<<<ct * row_blocks, 64 * waves, 0, stream>>>(g.row_ptr, g.col_idx, g.m, g.n, row_blocks, b,
                                                                L == 0 ? 1 : 0, upar);
         k_out_flags<<<(ct * kTile + 255) / 256, 256, 0, stream>>>(b, ct * kTile, L, upar, iters, ok);
-        k_out_tiles<false><<<ct * nchunks, 256, 0, stream>>>(b, g.n, L, ct * nchunks, post, bits, iters, ok);
+        k_out_tiles<<<ct * nchunks, 256, 0, stream>>>(b, g.n, L, ct * nchunks, post, bits, iters, ok);
     };
     auto iterate = [&](auto nt_tag) {
         constexpr bool NT = decltype(nt_tag)::value;
