@@ -926,10 +926,15 @@ constexpr int32_t kCompactMinTiles = 16; // chunks of fewer tiles are not compac
 // are packed into the first tiles, and the chunks left empty pass the further
 // phases in launches that find nothing to do (3 us each).  A phase's first
 // launches read the chunk's state from memory rather than from the Infinity
-// Cache, 7% slower, so four iterations make a phase.  n = 64800, 512 frames at
-// 1.6 dB (28 iterations on average, up to 50): 13.7 ms a chunk at a time, 11.5 ms
-// in phases.
-constexpr int32_t kPhaseFirst = 6, kPhase = 4;
+// Cache, 7% slower, so four iterations make a phase and eight the first one, in
+// which few frames stop (n = 64800, 512 frames at 1.6, 2.1 and 3 dB, with a first
+// phase of four: 11.52, 7.92 and 5.46 ms, of six 11.42, 8.06 and 5.99, of eight
+// 11.48, 7.88 and 5.42; a chunk at a time 14.24, 9.52 and 6.88); one or two at the
+// end join the phase before.  Up to twelve iterations the one plan saves less
+// than it costs (512 frames, 10 iterations: 3.28 ms a chunk at a time, 3.34 in
+// phases); up to 20 the phases cost 2% where no frame stops (512 frames at 1.6
+// dB: 6.28 and 6.42) and save 8% where they do (311 frames at 3 dB: 3.19 and 2.95).
+constexpr int32_t kPhaseFirst = 8, kPhase = 4, kPhaseLast = 3;
 
 } // namespace
 
@@ -1035,12 +1040,12 @@ int stream_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, u
                          (regular && g.stream_order.csc_edge) ? g.stream_order.csc_edge : g.csc_edge, g.n, g.E,
                          col_blocks, b, t, test_now);
         };
-        if (period > 0 && nt > 1 && chunk < kCompactMinTiles) { // phases
+        if (period > 0 && nt > 1 && chunk < kCompactMinTiles && L > kPhaseFirst + kPhase) { // phases
             const Bufs all = chunk_bufs(w, g, 0, true);
             k_ctrl_reset<<<1, 1, 0, stream>>>(w.ctrl);
             for (int32_t t0 = 0, t1; t0 < L; t0 = t1) {
                 t1 = t0 == 0 ? kPhaseFirst : t0 + kPhase;
-                if (t1 > L) t1 = L;
+                if (L - t1 < kPhaseLast) t1 = L;
                 for (int32_t c0 = 0; c0 < nt; c0 += chunk) {
                     const Bufs b = chunk_bufs(w, g, c0, t0 > 0);
                     for (int32_t t = t0 + 1; t <= t1; ++t) iteration(b, chunk < nt - c0 ? chunk : nt - c0, t);
