@@ -273,9 +273,11 @@ int ldpc_nms_decode(const ldpc_graph *g, const float *llr_dev, int32_t B, int32_
  * keeps, of every iteration, each row's two smallest magnitudes, their
  * positions and the signs (12 bytes, 16 and more for rows of more than 16
  * edges) and each bit's posterior for the backward, as long as all frames'
- * take at most 8 GiB, or at most what a checkpoint of the messages and
+ * take at most 8 GiB (256 MiB with `ckpt_every` above 2, which asks for memory
+ * rather than time), or at most what a checkpoint of the messages and
  * posteriors every `ckpt_every` iterations would take; beyond that the batch
  * is trained in passes and the backward runs the forward of each pass again.
+ * (State in the workspace, see below, is at least that of 64 frames.)
  *
  * ldpc_nms_train_forward: runs the T iterations with the weights (alpha_dev,
  * beta_dev: T x n_classes float32, device), writes the mean loss to

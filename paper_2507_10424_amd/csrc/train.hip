@@ -148,11 +148,14 @@ __global__ void k_adam(float *__restrict__ p, const float *__restrict__ g, float
 }
 
 // The workspace: the forward's records and posteriors of the whole batch where
-// they take no more than kKeepBytes or than a checkpoint of the messages every
-// K iterations would (with the per-frame state that such a backward needs);
-// beyond that, room for the frames of one pass, and the backward runs the
-// forward of each pass again.
-constexpr size_t kKeepBytes = (size_t)8 << 30;
+// they take no more than kKeepBytes (kSaveBytes) or than a checkpoint of the
+// messages every K iterations would (with the per-frame state that such a
+// backward needs); beyond that, room for the frames of one pass, and the backward
+// runs the forward of each pass again.  An interval above kTimeInterval asks for
+// memory rather than time (n = 1026, 8,000 frames, T = 10, intervals of 2, 3
+// and 10: 902, 526 and 269 MB, 0.90, 1.19 and 1.23 ms).
+constexpr size_t kKeepBytes = (size_t)8 << 30, kSaveBytes = (size_t)256 << 20;
+constexpr int32_t kTimeInterval = 2;
 struct Plan {
     bool lds = false;
     bool keep = true;    // the forward's records stay for the backward
@@ -169,11 +172,11 @@ Plan plan_of(const ldpc_graph &g, int32_t B, int32_t T, int32_t K) {
     const size_t ncls = g.class_degrees.size();
     p.lds = train_lds_fits(g);
     size_t budget = 4 * (size_t)B * (nck * nE + (p.lds ? 0 : 2 * nE + 2 * (size_t)g.n + K * nE));
-    budget = std::max(budget, kKeepBytes);
+    budget = std::max(budget, K <= kTimeInterval ? kKeepBytes : kSaveBytes);
     p.unit = p.lds ? train_lds_frame_bytes(g, T) : train_stream_tile_bytes(g, T, p.part);
     const size_t per = p.lds ? 1 : kTile, units = ((size_t)B + per - 1) / per;
-    p.keep = units * p.unit <= budget;
-    const size_t fit = p.keep ? units : std::max<size_t>(1, budget / p.unit);
+    const size_t fit = std::max<size_t>(1, budget / p.unit); // frames (tiles) of a pass
+    p.keep = units <= fit;
     p.pass = (int32_t)std::min<size_t>((size_t)B, fit * per);
     p.loss_parts = p.lds ? B : train_stream_loss_parts(g, B);
     p.grad_parts = p.lds ? B : train_stream_grad_parts(g, B);
@@ -186,7 +189,7 @@ Plan plan_of(const ldpc_graph &g, int32_t B, int32_t T, int32_t K) {
     p.off_loss = take(4 * (size_t)p.loss_parts * (p.lds ? 1 : T));
     p.off_gpart = take(4 * 2 * (size_t)T * ncls * (size_t)p.grad_parts);
     p.off_tmp = take(4 * kSumSlices * std::max<size_t>(1, 2 * (size_t)T * ncls));
-    p.off_units = take(fit * p.unit + 6 * 256);
+    p.off_units = take((p.keep ? units : fit) * p.unit + 6 * 256);
     p.total = off;
     return p;
 }
