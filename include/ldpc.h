@@ -277,7 +277,8 @@ int ldpc_nms_decode(const ldpc_graph *g, const float *llr_dev, int32_t B, int32_
  * rather than time), or at most what a checkpoint of the messages and
  * posteriors every `ckpt_every` iterations would take; beyond that the batch
  * is trained in passes and the backward runs the forward of each pass again.
- * (State in the workspace, see below, is at least that of 64 frames.)
+ * (State in the workspace, see below, is at least that of 64 frames.)  The size
+ * does not fall with B or T.
  *
  * ldpc_nms_train_forward: runs the T iterations with the weights (alpha_dev,
  * beta_dev: T x n_classes float32, device), writes the mean loss to

@@ -189,7 +189,8 @@ Plan plan_of(const ldpc_graph &g, int32_t B, int32_t T, int32_t K) {
     p.off_loss = take(4 * (size_t)p.loss_parts * (p.lds ? 1 : T));
     p.off_gpart = take(4 * 2 * (size_t)T * ncls * (size_t)p.grad_parts);
     p.off_tmp = take(4 * kSumSlices * std::max<size_t>(1, 2 * (size_t)T * ncls));
-    p.off_units = take((p.keep ? units : fit) * p.unit + 6 * 256);
+    // (in passes all that is allowed, so that no smaller B or T asks for more)
+    p.off_units = take((p.keep ? units * p.unit : std::max(budget, p.unit)) + 6 * 256);
     p.total = off;
     return p;
 }

@@ -1,5 +1,6 @@
-"""The training workspace (GPU): bounded by the checkpoint interval, and the same
-loss and gradients, bit for bit, with the records kept and in passes."""
+"""The training workspace (GPU): bounded by the checkpoint interval, not falling
+with the batch or the iterations, and the same loss and gradients, bit for bit,
+with the records kept and in passes."""
 import pytest
 
 from paper_2507_10424_amd import workloads as wl
@@ -32,6 +33,17 @@ def test_interval_bounds_the_workspace(graph):
             assert ldpc.train_workspace_bytes(g, B, T, K) <= max(256 * MIB, checkpoints) + sums(B, T)
         for K in (1, 2):
             assert ldpc.train_workspace_bytes(g, B, 10, K) <= max(8192 * MIB, -(-10 // K) * B * state) + sums(B, 10)
+
+
+def test_size_does_not_fall(graph):
+    _, ldpc, g = graph
+    for K in (2, 7):
+        for B in (3, 4096, 100000):
+            sizes = [ldpc.train_workspace_bytes(g, B, T, K) for T in range(1, 120)]
+            assert sizes == sorted(sizes), (K, B)
+        for T in (10, 100):
+            sizes = [ldpc.train_workspace_bytes(g, B, T, K) for B in range(1, 200000, 997)]
+            assert sizes == sorted(sizes), (K, T)
 
 
 def test_passes_give_the_kept_result(graph):
