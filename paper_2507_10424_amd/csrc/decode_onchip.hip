@@ -106,38 +106,56 @@ int pick(const ldpc_graph &g) {
 // Layout variants whose two-slot kernel takes more than 128 registers, so that
 // at most three of its waves share a SIMD: their one-slot form is the faster
 // one at every batch size (n = 1152, rows of 9, 20,000 frames: 0.406 ms with
-// two slots, 0.286 with one; rows of 12: 0.459 and 0.327).
+// two slots, 0.286 with one; rows of 12: 0.459 and 0.327) where the GPU holds
+// more workgroups of it (kernel_of).
 constexpr bool one_slot_always(int v) {
     return v == 23 || v == 27 || v == 29 || v == 31 || v == 33 || v == 37 || v == 39 || v == 41;
 }
 
 // The kernel for a regular graph's own row and column degree, -1 if there is
-// none.  Faster at every batch size than the padded layout's kernels, which
-// read six messages (four with rows of 16) of any bit, and than the
-// LDS-resident decoder, which takes rows of 8 and 10 otherwise (20 iterations,
-// 300 and 16,000 frames, before and now: (3,9) n = 2,007 0.047 and 0.522 ms,
-// 0.026 and 0.457; (3,12) n = 2,004 0.036 and 0.320, 0.017 and 0.215; (4,16)
-// n = 2,016 0.037 and 0.409, 0.019 and 0.251; (4,8) n = 2,008 0.062 and 1.389,
-// 0.042 and 0.701; (5,10) n = 1,010 0.049 and 1.028, 0.034 and 0.572).
+// none.  Faster than the padded layout's one-slot kernels, which read six
+// messages (four with rows of 16) of any bit, and than the LDS-resident decoder,
+// which takes rows of 8 and 10 otherwise (20 iterations, 300 and 16,000 frames,
+// before and now: (3,9) n = 2,007 0.047 and 0.522 ms, 0.026 and 0.457; (3,12) n =
+// 2,004 0.036 and 0.320, 0.017 and 0.215; (4,16) n = 2,016 0.037 and 0.409, 0.019
+// and 0.251; (4,8) n = 2,008 0.062 and 1.389, 0.042 and 0.701; (5,10) n = 1,010
+// 0.049 and 1.028, 0.034 and 0.572).
 int regular_form(const ldpc_graph &g) {
     for (int k = kFirstRegular; k < kNumKernels; ++k)
         if (variant_ok(g, k)) return k;
     return -1;
 }
 
+int64_t room_of(const ldpc_graph &g, int v, bool learned) { // resident workgroups, with the compiler's registers
+    const KernelFn fn = v >= kNumVariants ? kKernelsOne[learned ? 1 : 0][v - kNumVariants] : kKernels[0][learned ? 1 : 0][v];
+    return resident_workgroups((const void *)fn, threads_for(g, kVariants[v]), lds_of(g, v), g);
+}
+
 // The kernel (index into kVariants) that decodes B frames: the picked variant,
-// or, without a tuning record, its one-slot form, whose rounds are about half
-// as long, while no more than four frames fall to each resident workgroup of
-// it ((3,6) n = 1024, B = 1,000: 0.069 ms with two slots and 0.045 with one;
-// 4,000: 0.097 and 0.092; 20,000: 0.233 and 0.253).
-int kernel_of(const ldpc_graph &g, int64_t B, bool learned) {
-    const int v = pick(g), o = v >= 0 ? one_slot(v) : -1;
-    if (onchip_regular(g)) return regular_form(g);
+// or, without a tuning record, its one-slot form or the regular graph's own,
+// whose rounds are about half as long, while no more than four frames fall to
+// each resident workgroup of it ((3,6) n = 1024, B = 1,000: 0.069 ms with two
+// slots and 0.045 with one; 4,000: 0.097 and 0.092; 20,000: 0.233 and 0.253), and
+// at every size where the two-slot kernel is short of registers.  Rows of 9 and
+// workgroups of more than four wavefronts are the exception: a CU holds one
+// workgroup of either kernel, so that the one-slot form decodes half the frames
+// at a time.  There it is taken while two frames fall to each (eight where
+// plain decoding stops early and a stopped frame's slot weighs most, any number
+// for a regular graph's own) and where other launches fill the GPU.  (12
+// iterations, two slots and one, 8,000 frames: (3,9) n = 1800 plain 0.249 and
+// 0.228 ms, learned 0.275 and 0.294, learned to the end 0.501 and 0.560; columns
+// of 2, 3 and 6, n = 2304, 0.242 and 0.264, 0.277 and 0.329, 0.445 and 0.559; 300
+// frames 0.045 and 0.027, 0.052 and 0.031, 0.060 and 0.041.)
+int kernel_of(const ldpc_graph &g, int64_t B, bool learned, bool early, bool shared = false) {
+    const int v = pick(g), r = onchip_regular(g) ? regular_form(g) : -1;
+    const int o = r >= 0 ? r : v >= 0 ? one_slot(v) : -1;
     if (g.tuned() || o < 0 || !variant_ok(g, o)) return v;
-    if (one_slot_always(v)) return o;
-    const int64_t room = resident_workgroups((const void *)kKernelsOne[learned ? 1 : 0][o - kNumVariants],
-                                             threads_for(g, kVariants[o]), lds_of(g, o), g);
-    return B <= 4 * room ? o : v;
+    if (r >= 0 && (v < 0 || !kVariants[v].rx)) return r; // (no two-slot kernel for rows of its degree)
+    const int64_t room = room_of(g, o, learned);
+    if (r < 0 && !one_slot_always(v)) return B <= 4 * room ? o : v;
+    if (shared || 4 * room >= 5 * room_of(g, v, learned)) return o;
+    if (!learned && early) return r >= 0 || B <= 8 * room ? o : v;
+    return B <= 2 * room ? o : v;
 }
 KernelFn kernel_fn(const ldpc_graph &g, int v, bool learned) {
     return v >= kNumVariants ? kKernelsOne[learned ? 1 : 0][v - kNumVariants]
@@ -331,7 +349,8 @@ int onchip_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, u
     (void)T;
     if (!onchip_fits(g) && !onchip_regular(g)) return LDPC_EUNSUPPORTED;
     if (ws == nullptr || ws_bytes < onchip_workspace_bytes(g, B)) return LDPC_EWORKSPACE;
-    const int v = kernel_of(g, B, alpha != nullptr);
+    const int32_t early = test_period(flags);
+    const int v = kernel_of(g, B, alpha != nullptr, early > 0);
     const KernelFn fn = kernel_fn(g, v, alpha != nullptr);
     const int threads = threads_for(g, kVariants[v]), per_wg = v >= kNumVariants ? 1 : 2 * kVariants[v].f;
     const size_t lds = lds_of(g, v);
@@ -339,7 +358,6 @@ int onchip_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, u
     int st = launch_grid((const void *)fn, threads, lds, g, B, g.tuned() ? g.tuning.wg_per_cu : 0, &grid,
                          per_wg);
     if (st) return st;
-    const int32_t early = test_period(flags);
     JobTable jt{};
     jt.njobs = 1;
     Job &J = jt.job[0] = make_job(g, v, llr, B, bits, post, iters, ok, alpha, beta, (uint32_t *)ws);
@@ -390,7 +408,7 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
         const ldpc_graph &g = *jb.g;
         if (!onchip_fits(g)) return LDPC_EUNSUPPORTED;
         if (jb.B == 0) continue;
-        const int v_own = kernel_of(g, jb.B, false);
+        const int v_own = kernel_of(g, jb.B, false, test_period(flags) > 0, njobs > 1);
         int v = v_own;
         if (!shared_launch_ok(v)) // another variant that fits keeps the job eligible for the shared launch
             for (int c : kPickOrder)

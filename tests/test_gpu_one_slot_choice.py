@@ -1,0 +1,79 @@
+"""Which on-chip kernel decodes a batch without a tuning record (GPU): rows of 9
+on either side of the choices between one and two frame slots (workgroups of
+four and of more wavefronts, plain and learned, with and without early exit),
+batches between the workgroups that run at once and those that the runtime
+promises, and jobs of a multi-code call alone and together.  Every frame against
+the streaming path, some against the oracle."""
+import numpy as np
+import pytest
+
+from paper_2507_10424_amd import workloads as wl
+from parity import assert_parity, note, oracle_decode
+
+pytestmark = pytest.mark.gpu
+
+
+def qc(Z, mb):
+    return wl.qc_irregular_ldpc(24, mb, Z, np.concatenate([np.full(12, 2), np.full(8, 3), np.full(4, min(6, mb))]),
+                                seed=9)
+
+
+CODES = {
+    "regular_9_four_waves": lambda: wl.regular_ldpc(1404, 468, 3, 9, seed=2),
+    "regular_9_five_waves": lambda: wl.regular_ldpc(1800, 600, 3, 9, seed=2),
+    "profile_9_six_waves": lambda: qc(96, 8),
+    "padded_9_five_waves": lambda: wl.regular_ldpc(1800, 400, 2, 9, seed=2),
+    "regular_12_five_waves": lambda: wl.regular_ldpc(1200, 300, 3, 12, seed=2),
+}
+
+
+@pytest.mark.parametrize("learned", [False, True])
+@pytest.mark.parametrize("name", sorted(CODES))
+def test_either_side(name, learned):
+    import torch
+    from paper_2507_10424_amd import ldpc
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dev = torch.device("cuda:0")
+    H = CODES[name]()
+    n, L = H.shape[1], 8
+    rate = 1.0 - H.shape[0] / n
+    g = ldpc.build_graph(torch.from_numpy(H).to(dev))
+    rng = np.random.default_rng(5)
+    w = [rng.uniform(0.6, 1.1, size=(L, 1)).astype(np.float32), rng.uniform(0.0, 0.3, size=(L, 1)).astype(np.float32)]
+    wd = [torch.from_numpy(x).to(dev) for x in w]
+    # one and two workgroups of frames for every CU, and past the choices' thresholds
+    for B in (257, 511, 513, 1025, 1100, 2049):
+        llr = wl.bpsk_awgn_llr_torch(None, 2.5 + 5.5 * (rate - 0.5), rate, B, dev, n=n, batch=B)
+        for flags in (0, ldpc.LDPC_NO_EARLY_EXIT):
+            note(f"[one slot] {name} B={B} flags={flags} learned={learned}")
+            run = (lambda f: ldpc.nms_decode(g, llr, L, *wd, flags=f)) if learned else \
+                  (lambda f: ldpc.minsum_decode(g, llr, L, flags=f))
+            out, ref = run(flags), run(flags | ldpc.LDPC_FORCE_STREAM)
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(out, ref)), (B, flags)
+            if B in (257, 1025):
+                some = np.r_[0:3, B - 3:B]
+                assert_parity(tuple(t.cpu().numpy()[some] for t in out),
+                              oracle_decode(H, llr.cpu().numpy()[some], L, flags, *(w if learned else ())), f"B={B}")
+
+
+@pytest.mark.parametrize("batches", [(51,), (1638, 51), (1638, 51, 40), (5, 3, 700), (4915, 153, 2457)])
+def test_jobs(batches):
+    import torch
+    from paper_2507_10424_amd import ldpc
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dev = torch.device("cuda:0")
+    fam = wl.qc_multi_code_family()
+    jobs = []
+    for k, B in enumerate(batches):
+        c = fam[k]
+        jobs.append((ldpc.build_graph(torch.from_numpy(c["H"]).to(dev)),
+                     wl.bpsk_awgn_llr_torch(None, 2.0 + 5.5 * (c["rate"] - 0.5), c["rate"], k, dev, n=c["n"], batch=B)))
+    for _ in range(3):
+        outs = ldpc.minsum_decode_multi(jobs, 15)
+        for (g, llr), out in zip(jobs, outs):
+            ref = ldpc.minsum_decode(g, llr, 15, flags=ldpc.LDPC_FORCE_STREAM)
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(out, ref))
