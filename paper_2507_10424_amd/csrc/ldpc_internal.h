@@ -252,29 +252,37 @@ inline int workgroups_per_cu(int waves, int per_simd, int most) {
 
 // Resident workgroups of a kernel on the graph's GPU (at least one per CU), with
 // its dynamic LDS allowed up to the GPU's limit; -1 on failure.  Each thread
-// remembers the answers (they depend on nothing else), which take two calls
-// into the runtime.  With the binding's stream getter and device guard, which
+// remembers the answers (they depend on nothing else), which take three calls
+// into the runtime.  (With the binding's stream getter and device guard, which
 // cost as much: a call on one frame of (3,6) n = 1024 10.1 us of host time
-// before and 5.8 after.
-inline int64_t resident_workgroups(const void *fn, int threads, size_t lds, const ldpc_graph &g) {
+// before and 5.8 after.)  `promised`: as many as the runtime answers; a launch of
+// no more than these, each for the frames dealt to it alone, does without frame
+// counters, and those that do not run at once follow as the first ones end.
+inline int64_t resident_workgroups(const void *fn, int threads, size_t lds, const ldpc_graph &g,
+                                   int64_t *promised = nullptr) {
     struct Entry {
         const void *fn;
         size_t lds;
         int threads, device;
-        int64_t count;
+        int64_t count, promised;
     };
     constexpr size_t kEntries = 64;
     static thread_local Entry cache[kEntries] = {};
     const size_t h = ((size_t)fn / 16 + lds / 16 * 7 + (size_t)threads * 31 + (size_t)g.device) % kEntries;
     Entry &e = cache[h];
-    if (e.fn == fn && e.lds == lds && e.threads == threads && e.device == g.device) return e.count;
+    if (e.fn == fn && e.lds == lds && e.threads == threads && e.device == g.device) {
+        if (promised) *promised = e.promised;
+        return e.count;
+    }
     int per_cu = 0, per_simd = 0; // (a workgroup of four waves has one on each SIMD)
     if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, g.lds_max) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_simd, fn, 256, 0) != hipSuccess)
         return -1;
-    per_cu = workgroups_per_cu((threads + 63) / 64, per_simd, per_cu);
-    e = Entry{fn, lds, threads, g.device, (int64_t)(per_cu < 1 ? 1 : per_cu) * g.num_cu};
+    const int runs = workgroups_per_cu((threads + 63) / 64, per_simd, per_cu);
+    e = Entry{fn, lds, threads, g.device, (int64_t)(runs < 1 ? 1 : runs) * g.num_cu,
+              (int64_t)(per_cu < 1 ? 1 : per_cu) * g.num_cu};
+    if (promised) *promised = e.promised;
     return e.count;
 }
 
