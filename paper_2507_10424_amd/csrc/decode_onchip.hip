@@ -410,6 +410,7 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
         int wg_per_cu; // tuned cap, 0 for none
     };
     std::vector<Own> own;
+    Own sharer{};
     int32_t nj = 0;
     for (int32_t k = 0; k < njobs; ++k) {
         const ldpc_job &jb = jobs[order[k]];
@@ -434,12 +435,12 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
             const int64_t in_flight = room * kVariants[v_own].f;
             alone = (int64_t)jb.B >= kOwnLaunchRounds * in_flight;
         }
-        if (alone) {
-            own.push_back(Own{make_job(g, v_own, jb.llr_dev, jb.B, jb.bits_dev, jb.post_dev, jb.iters_dev, jb.ok_dev,
-                                       nullptr, nullptr, queues + (size_t)k * kQueueWords),
-                              fn, t_own, l_own, &g, g.tuned() ? g.tuning.wg_per_cu : 0});
-            continue;
-        }
+        own.push_back(Own{make_job(g, v_own, jb.llr_dev, jb.B, jb.bits_dev, jb.post_dev, jb.iters_dev, jb.ok_dev,
+                                   nullptr, nullptr, queues + (size_t)k * kQueueWords),
+                          fn, t_own, l_own, &g, g.tuned() ? g.tuning.wg_per_cu : 0});
+        if (alone) continue;
+        sharer = own.back();
+        own.pop_back();
         const int t = threads_for(g, kVariants[v]);
         threads = t > threads ? t : threads;
         lds = lds_of(g, v) > lds ? lds_of(g, v) : lds;
@@ -447,6 +448,14 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
         any = &g;
         jt.job[nj++] = make_job(g, v, jb.llr_dev, jb.B, jb.bits_dev, jb.post_dev, jb.iters_dev, jb.ok_dev, nullptr,
                                 nullptr, queues + (size_t)k * kQueueWords);
+    }
+    // A job that would share with none runs its own kernel too (four frames of it
+    // in turn to a workgroup otherwise: two quasi-cyclic codes, 1,638 and 51
+    // frames, 0.158 ms with the 51 in the shared kernel, 0.132 in their own).
+    if (nj == 1) {
+        own.push_back(sharer);
+        nj = 0;
+        frames = 0;
     }
     jt.njobs = nj;
     const int32_t early = test_period(flags);
@@ -502,11 +511,12 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
     for (Launch &x : launches)
         if (x.jt.njobs == 1) deal(x.jt.job[0], x.grid, launches.size() == 1 ? 2 : 1);
     SideStreams *side = launches.size() > 1 ? side_streams() : nullptr;
+    const int sides = (int)std::min<size_t>(kSideStreams, launches.size() - 1); // of the side streams, those in use
     std::unique_lock<std::mutex> hold;
     if (side) {
         hold = std::unique_lock<std::mutex>(side->mu);
         LDPC_HIP_TRY(hipEventRecord(side->fork, stream));
-        for (int k = 0; k < kSideStreams; ++k) LDPC_HIP_TRY(hipStreamWaitEvent(side->s[k], side->fork, 0));
+        for (int k = 0; k < sides; ++k) LDPC_HIP_TRY(hipStreamWaitEvent(side->s[k], side->fork, 0));
     }
     for (size_t k = 0; k < launches.size(); ++k) {
         const Launch &x = launches[k];
@@ -514,7 +524,7 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
         timed_launch(K_ONCHIP, x.fn, x.grid, x.threads, x.lds, on, x.jt, L, early);
     }
     if (side) {
-        for (int k = 0; k < kSideStreams; ++k) {
+        for (int k = 0; k < sides; ++k) {
             LDPC_HIP_TRY(hipEventRecord(side->join[k], side->s[k]));
             LDPC_HIP_TRY(hipStreamWaitEvent(stream, side->join[k], 0));
         }
