@@ -503,20 +503,30 @@ int lds_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, uint
     if (!choose(1)) return LDPC_EHIP;
     // Two frames per workgroup where many frames wait for each: the LDS moves a
     // pair of frames for little more than one, but a frame alone finishes
-    // sooner and is replaced at less cost.  With rows of at most 8 and up to three
-    // workgroups per CU, at once (one per CU: (3,6) n = 4096, 1,500 frames 0.158 ms
-    // with one and 0.143 with two; two and three per CU go either way: (4,5) n =
-    // 1000, 10,000 frames 1.08 and 0.82, rows of at most 8, n = 1000, 0.272 and
-    // 0.267, n = 1200, 0.396 and 0.464); with rows above 8 (whose kernel for two
-    // spills) and with four workgroups per CU and more, late (irregular n = 4000:
-    // 777 frames 0.180 and 0.256 ms, 6,000 frames 0.806 and 0.814; (4,8) n = 600:
-    // 15,000 frames 0.642 and 0.766; (5,10) n = 1000, 15,000 frames that do not
-    // converge: 2.17 and 1.77).
+    // sooner and is replaced at less cost.  Where one workgroup fills a CU and
+    // rows are short, at once ((3,6) n = 4096, 1,500 frames: 0.158 ms with one
+    // and 0.143 with two; (4,5) n = 1000, 10,000 frames 1.08 and 0.82); with rows
+    // above 8 (whose kernel for two spills) and with four workgroups per CU and
+    // more, late (irregular n = 4000: 777 frames 0.180 and 0.256 ms, 6,000 frames
+    // 0.806 and 0.814; (4,8) n = 600: 15,000 frames 0.642 and 0.766; (5,10) n =
+    // 1000, 15,000 frames that do not converge: 2.17 and 1.77).  With two or three
+    // per CU and short rows, only where the GPU then holds more frames, and all of
+    // them or many times as many (rows of at most 8, 20 iterations: n = 1200, two
+    // per CU and one of two frames, 600 frames 0.057 and 0.073 ms, 10,000 0.396
+    // and 0.463; n = 1000, three and two, 800 frames 0.051 and 0.044, 1,600 0.073
+    // and 0.088, 10,000 0.272 and 0.267).
     int F = 1;
-    const int64_t queued = g.dc_max > 8 ? 8 : room >= 4 * (int64_t)g.num_cu ? 32 : 1;
+    const int64_t per_cu = room / g.num_cu;
+    const bool few = g.dc_max <= 8 && (per_cu == 2 || per_cu == 3);
+    const int64_t queued = g.dc_max > 8 ? 8 : per_cu >= 4 ? 32 : 1;
     if (B > queued * room && g.dc_max <= 16 && cpt <= 8 && lds_bytes(g, 2) <= (size_t)g.lds_max) {
+        const int64_t held = room; // frames, with one per workgroup
         F = 2;
         if (!choose(2)) return LDPC_EHIP;
+        if (few && (2 * room <= held || (B > 2 * room && B <= 4 * held))) {
+            F = 1;
+            if (!choose(1)) return LDPC_EHIP;
+        }
     }
     const int64_t groups = ((int64_t)B + F - 1) / F;
     // (rows of up to 16, n = 600, 800 frames: 0.045 ms with 800 workgroups of which
