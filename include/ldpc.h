@@ -222,14 +222,14 @@ size_t ldpc_multi_workspace_bytes(int32_t njobs);
  * must fit the on-chip kernel and live on the current device.  Jobs whose
  * batch alone fills the GPU run as launches of their own kernels (with the
  * graph's tuning record), one launch for all such jobs of the same kernel and
- * launch shape (the same graph, or graphs of one shape); the others share one
- * persistent launch.  In each launch workgroups take frames from per-job
- * counters, largest job (frames x edges) first, and move to the next job
- * without waiting for the others.  Several launches run side by side: the
- * first on `stream`, the others on side streams that the library creates
- * once per device (default priority) and forks from `stream` and joins back
- * into it in this call, so that the call is ordered on `stream` like one
- * kernel.  Calls on one device take a lock while they enqueue.  The first
+ * launch shape (the same graph, or graphs of one shape), and so does a job that
+ * would share with none; the others share one persistent launch.  In each
+ * launch workgroups take frames from per-job counters, largest job (frames x
+ * edges) first, and move to the next job without waiting for the others.
+ * Several launches run side by side: the first on `stream`, the others on side
+ * streams that the library creates once per device (default priority) and forks
+ * from `stream` and joins back into it in this call, so that the call is ordered
+ * on `stream` like one kernel.  Calls on one device take a lock while they enqueue.  The first
  * call on a device that needs them creates the side streams: make it before
  * capturing such a call into a HIP graph (a capture records the fork and the
  * join as graph dependencies).
@@ -336,11 +336,12 @@ int ldpc_adam_step(float *param_dev, const float *grad_dev, float *m1_dev, float
  * Launch choices of a graph ("tuning record").  Without one, decoding takes
  * the on-chip path whenever the graph fits with rows of one degree (the
  * preferred fitting kernel variant: exact degrees, then the tightest degree
- * masks, two frame slots, one for small batches; as many workgroups as fit on
- * each CU), else the LDS-resident decoder for graphs whose n posteriors and E
- * messages fit one CU's LDS with rows of at most 32 edges (its workspace is
- * the on-chip path's where the graph fits that, else the streaming path's),
- * and otherwise the streaming path with 4 wavefronts per workgroup.
+ * masks, two frame slots, one for small batches and where the kernel for two
+ * is short of registers; as many workgroups as each CU runs), else the
+ * LDS-resident decoder for graphs whose n posteriors and E messages fit one CU's
+ * LDS with rows of at most 32 edges (its workspace is the on-chip path's where
+ * the graph fits that, else the streaming path's), and otherwise the streaming
+ * path with 4 wavefronts per workgroup.
  *   path          1 on-chip, 2 streaming (0 in ldpc_graph_get_tuning: none set)
  *   variant       on-chip kernel variant (degree templates, rows and bits
  *                 per thread, frame slots), -1 for the preferred one

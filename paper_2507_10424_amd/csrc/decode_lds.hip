@@ -18,11 +18,11 @@
 // one frame and 24 with two (gfx950: 7 / 7.5 cycles per gathered b32 / b64
 // read, 2.5 per consecutive one, 4.3 / 6.3 per write), against about 11 VALU
 // instructions per frame: the LDS bounds it, which is why two frames share a
-// workgroup where they fit.  The streaming decoder moves 12 (E + n) bytes per
+// workgroup where they fit and enough frames wait (lds_decode).  The streaming decoder moves 12 (E + n) bytes per
 // frame-iteration through the Infinity Cache instead, two launches each, and
 // runs a tile of 64 frames until its last one stops.  Whole calls, streaming
 // before and this kernel now: n = 8176, rows of 32, 1,500 frames, 2.78 ms and
-// 0.276 ms; n = 4000, rows of 2 to 14, 777 frames, 1.57 and 0.162 ms; the
+// 0.276 ms; n = 4000, rows of 2 to 14, 777 frames, 1.57 and 0.156 ms; the
 // (3,6) code of n = 4096, 333 frames, 20 iterations, 0.340 and 0.071 ms.
 //
 // Row arithmetic, order of the sums, tests and outputs are those of the

@@ -743,8 +743,8 @@ __global__ __launch_bounds__(256) void k_from_tiles(const float *__restrict__ r,
 // XCD keeps some), the rest of that set's slots are marked empty, and the
 // chunk continues in that set (the kernels take the set from the control
 // words: the set of the last plan, the other one if it went ahead).  Each
-// frame's own
-// arithmetic is unchanged: it sees the same launches in the same order.
+// frame's own arithmetic is unchanged: it sees the same launches in the same
+// order.
 constexpr int kPlanThreads = 1024;
 constexpr int kMoveRows = 128; // rows of r, s and eta per wavefront of the copy
 

@@ -23,8 +23,8 @@
 // Measured on one MI355X (frames drawn, loss and gradients of a batch; before:
 // a workgroup of 256 threads per frame, its state in LDS or in device memory,
 // that kept the messages of every ckpt_every-th iteration and ran the forward
-// again in between): n = 1024, 4,096 frames, T = 10: 1.97 -> 0.367 ms; n =
-// 64800, 96 frames, T = 10: 51.1 -> 1.63 ms.
+// again in between): n = 1024, 4,096 frames, T = 10: 1.97 -> 0.355 ms; n =
+// 64800, 96 frames, T = 10: 51.1 -> 1.62 ms.
 #include <algorithm>
 
 #include "train_internal.h"

@@ -110,7 +110,7 @@ struct TrainStream {
     float *r, *eta, *gs, *gr; // [tile][n | E | n | n][64]; the backward keeps gx in eta
     float *s;                 // [tile][T][n][64]
     uint32_t *rec;            // [tile][T][m][words][64]
-    float *loss_part;         // [T][blocks]: block_count() per iteration of the whole batch
+    float *loss_part;         // [T][parts]: train_stream_loss_parts() of the whole batch per iteration
     float *gpart;             // [2][T][ncls][waves]
 };
 size_t train_stream_tile_bytes(const ldpc_graph &g, int32_t T, size_t part[6]);

@@ -8,7 +8,7 @@
 // iteration for the check update, about 20 for the record, 3 per bit, and the
 // softplus of every posterior (38); backward: about 10 per edge and the sigmoid
 // (29) per bit.  Memory: 10 KB per frame and iteration written, then read
-// (2.8 and 2.1 TB/s in the two kernels, 0.151 and 0.204 ms for 4,096 frames).
+// (2.6 and 2.1 TB/s in the two kernels, 0.159 and 0.200 ms for 4,096 frames).
 #include <algorithm>
 
 #include "lds_common.h"
@@ -435,7 +435,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
                 for (int c = 0; c < CPT; ++c) sn[c] = w + c * nw < J.t.bit_groups ? sv[tr + c * nt] : 0.0f;
             }
             __syncthreads();
-            // the previous iteration's sums over the rows (written before the last barrier but one)
             float ga[NC], gb[NC];
 #pragma unroll
             for (int c = 0; c < NC; ++c) ga[c] = gb[c] = 0.0f;
