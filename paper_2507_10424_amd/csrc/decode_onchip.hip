@@ -215,15 +215,21 @@ void deal(Job &J, int grid, int rounds) {
 
 // Grid of a persistent launch: every CU filled to its occupancy, but no more
 // workgroups than there are groups of `per_wg` frames.  `rounds` frames of each
-// workgroup may be dealt: a few workgroups more than run at once if every frame
-// is dealt so ((3,12) n = 1200, 1,100 frames: 0.0297 ms with the
-// 512 that run at once and counters, 0.0251 with 550 and none).
+// workgroup may be dealt: where that is every frame, up to the runtime's count of
+// workgroups, since those that wait for a CU take it as the first ones end (n =
+// 2304, rows of 9, 430 frames: 0.076 ms with 430, 0.093 with the 256 that run at
+// once and two frames to each; (3,12) n = 1200, 1,100 frames to the end, 512 at
+// once and 768: 0.060 ms with 768, 0.072 with 550).  `among`: other launches share
+// the GPU, and the grid is the runtime's count: workgroups waiting for a CU take
+// it from launches that end (the eight quasi-cyclic codes at 0.3 of their
+// batches, 1.5 dB: 0.599 ms, 0.668 with those that run at once).
 int launch_grid(const void *fn, int threads, size_t lds, const ldpc_graph &g, int64_t frames, int cap_per_cu,
-                int *grid, int per_wg, int rounds = 0) {
+                int *grid, int per_wg, int rounds = 0, bool among = false) {
     int64_t promised = 0, want = resident_workgroups(fn, threads, lds, g, &promised);
     if (want < 0) return LDPC_EHIP;
-    if (rounds > 0 && cap_per_cu == 0 && frames > rounds * want && frames <= rounds * promised) {
-        *grid = (int)((frames + rounds - 1) / rounds);
+    if (among) want = promised;
+    if (rounds > 0 && cap_per_cu == 0 && frames <= rounds * promised) {
+        *grid = (int)std::min(frames, promised);
         return LDPC_OK;
     }
     if (cap_per_cu > 0) want = std::min(want, (int64_t)g.num_cu * cap_per_cu);
@@ -389,11 +395,13 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
         return (int64_t)jobs[a].B * jobs[a].g->E > (int64_t)jobs[b].B * jobs[b].g->E;
     });
-    // A job whose batch alone fills every CU at least once gets a launch of
-    // its own kernel (its own LDS size, workgroup size, register budget and
-    // tuned workgroups per CU); so does a job that only the widest variant
-    // fits.  The other jobs share one persistent launch, whose workgroup size
-    // and LDS are the maxima over them.
+    // A job whose batch alone fills every CU at least once (by the runtime's
+    // count: three of the eight codes at 0.07 of their batches 0.084 ms, 0.112
+    // with the 430 frames of n = 2304 in a launch of their own, of which 256 run
+    // at once and 512 by that count) gets a launch of its own kernel (its own LDS
+    // size, workgroup size, register budget and tuned workgroups per CU); so does
+    // a job that only the widest variant fits.  The other jobs share one
+    // persistent launch, whose workgroup size and LDS are the maxima over them.
     constexpr int64_t kOwnLaunchRounds = 1;
     JobTable jt{};
     int threads = 64;
@@ -430,8 +438,8 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
         const size_t l_own = lds_of(g, v_own);
         bool alone = !shared_launch_ok(v);
         if (!alone) {
-            const int64_t room = resident_workgroups((const void *)fn, t_own, l_own, g);
-            if (room < 0) return LDPC_EHIP;
+            int64_t room = 0;
+            if (resident_workgroups((const void *)fn, t_own, l_own, g, &room) < 0) return LDPC_EHIP;
             const int64_t in_flight = room * kVariants[v_own].f;
             alone = (int64_t)jb.B >= kOwnLaunchRounds * in_flight;
         }
@@ -467,9 +475,12 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
     // frames overlap the next job's first ones.
     struct Launch {
         KernelFn fn;
-        int grid, threads;
+        int threads;
         size_t lds;
         JobTable jt;
+        const ldpc_graph *g;
+        int64_t frames;
+        int wg_per_cu, per_wg, grid;
     };
     std::vector<Launch> launches;
     std::vector<bool> placed(own.size(), false);
@@ -489,28 +500,24 @@ int onchip_decode_multi(const ldpc_job *jobs, int32_t njobs, int32_t L, uint32_t
             l = own[b].lds > l ? own[b].lds : l;
             fr += own[b].J.B;
         }
-        int grid = 0;
-        const int st = launch_grid((const void *)own[a].fn, t, l, *own[a].g, fr, own[a].wg_per_cu, &grid,
-                                   ot.njobs == 1 && own[a].J.variant >= kNumVariants
-                                       ? 1
-                                       : 2 * kVariants[own[a].J.variant].f);
-        if (st) return st;
-        launches.push_back(Launch{own[a].fn, grid, t, l, ot});
+        const int per_wg = ot.njobs == 1 && own[a].J.variant >= kNumVariants ? 1 : 2 * kVariants[own[a].J.variant].f;
+        launches.push_back(Launch{own[a].fn, t, l, ot, own[a].g, fr, own[a].wg_per_cu, per_wg, 0});
     }
-    if (frames > 0) {
-        int grid = 0;
-        const int st = launch_grid((const void *)k_onchip_multi, threads, lds, *any, frames, 0, &grid, 4);
-        if (st) return st;
-        launches.push_back(Launch{k_onchip_multi, grid, threads, lds, jt});
-    }
+    if (frames > 0) launches.push_back(Launch{k_onchip_multi, threads, lds, jt, any, frames, 0, 4, 0});
     // Several launches run side by side: all but the first go round-robin to
     // the library's side streams of the device, which wait for everything
     // enqueued on `stream` so far and which `stream` waits for at the end.
     // Each launch's last frames (and the shared launch of small jobs) then
     // overlap the others instead of leaving CUs idle.
-    for (Launch &x : launches)
-        if (x.jt.njobs == 1) deal(x.jt.job[0], x.grid, launches.size() == 1 ? 2 : 1);
-    SideStreams *side = launches.size() > 1 ? side_streams() : nullptr;
+    const bool among = launches.size() > 1;
+    for (Launch &x : launches) {
+        const int rounds = among ? 1 : 2; // dealt to each workgroup of a one-slot kernel for one job
+        const int st = launch_grid((const void *)x.fn, x.threads, x.lds, *x.g, x.frames, x.wg_per_cu, &x.grid, x.per_wg,
+                                   x.per_wg == 1 ? rounds : 0, among);
+        if (st) return st;
+        if (x.jt.njobs == 1) deal(x.jt.job[0], x.grid, rounds);
+    }
+    SideStreams *side = among ? side_streams() : nullptr;
     const int sides = (int)std::min<size_t>(kSideStreams, launches.size() - 1); // of the side streams, those in use
     std::unique_lock<std::mutex> hold;
     if (side) {
