@@ -133,29 +133,34 @@ int64_t room_of(const ldpc_graph &g, int v, bool learned) { // resident workgrou
 
 // The kernel (index into kVariants) that decodes B frames: the picked variant,
 // or, without a tuning record, its one-slot form or the regular graph's own,
-// whose rounds are about half as long, while no more than four frames fall to
-// each resident workgroup of it ((3,6) n = 1024, B = 1,000: 0.069 ms with two
-// slots and 0.045 with one; 4,000: 0.097 and 0.092; 20,000: 0.233 and 0.253), and
-// at every size where the two-slot kernel is short of registers.  Rows of 9 and
-// workgroups of more than four wavefronts are the exception: a CU holds one
-// workgroup of either kernel, so that the one-slot form decodes half the frames
-// at a time.  There it is taken while two frames fall to each (eight where
-// plain decoding stops early and a stopped frame's slot weighs most, any number
-// for a regular graph's own) and where other launches fill the GPU.  (12
-// iterations, two slots and one, 8,000 frames: (3,9) n = 1800 plain 0.249 and
-// 0.228 ms, learned 0.275 and 0.294, learned to the end 0.501 and 0.560; columns
-// of 2, 3 and 6, n = 2304, 0.242 and 0.264, 0.277 and 0.329, 0.445 and 0.559; 300
-// frames 0.045 and 0.027, 0.052 and 0.031, 0.060 and 0.041.)
+// whose rounds are about half as long, while no more than four frames (five where
+// they stop early, and a slot waits less for its neighbour) fall to each resident
+// workgroup of it ((3,6) n = 1024, B = 1,000: 0.069 ms with two slots and 0.045
+// with one; 4,000: 0.097 and 0.092; 20,000: 0.233 and 0.253; early exit, n = 576,
+// rows of 6, 6,000 of 1,280 at a time, 0.137 and 0.123; to the end, n = 1530, 2,500
+// of 512, 0.094 and 0.113), and at every size where the two-slot kernel is short of
+// registers.  Rows of 9 and workgroups of more than four wavefronts are the
+// exception: a CU holds one workgroup of either kernel, so that the one-slot form
+// decodes half the frames at a time.  There it is taken at every size for a
+// regular graph's own and plain decoding, and where other launches fill the GPU;
+// else while the frames of each workgroup are few: 12 where they stop early (6
+// for a profile's learned decoding), 3 where they do not (6 for a regular graph's
+// own).  (Two slots and one, (3,9) n = 1800: to the end, 600 frames 0.063 and 0.049
+// ms, 20,000 1.12 and 1.08; learned, 2,600 frames 0.207 and 0.203, 7,000 0.462 and
+// 0.484; learned to the end, 1,200 frames 0.101 and 0.095, 7,000 0.441 and 0.494.
+// Columns of 2, 3 and 6, n = 2304: early exit, 2,100 frames 0.216 and 0.193, 7,000
+// 0.471 and 0.513; learned, 1,200 frames 0.131 and 0.128, 7,000 0.480 and 0.575; to
+// the end, 600 frames 0.057 and 0.051, 7,000 0.343 and 0.398.)
 int kernel_of(const ldpc_graph &g, int64_t B, bool learned, bool early, bool shared = false) {
     const int v = pick(g), r = onchip_regular(g) ? regular_form(g) : -1;
     const int o = r >= 0 ? r : v >= 0 ? one_slot(v) : -1;
     if (g.tuned() || o < 0 || !variant_ok(g, o)) return v;
     if (r >= 0 && (v < 0 || !kVariants[v].rx)) return r; // (no two-slot kernel for rows of its degree)
     const int64_t room = room_of(g, o, learned);
-    if (r < 0 && !one_slot_always(v)) return B <= 4 * room ? o : v;
-    if (shared || 4 * room >= 5 * room_of(g, v, learned)) return o;
-    if (!learned && early) return r >= 0 || B <= 8 * room ? o : v;
-    return B <= 2 * room ? o : v;
+    if (r < 0 && !one_slot_always(v)) return B <= (early ? 5 : 4) * room ? o : v;
+    if (shared || (r >= 0 && !learned) || 4 * room >= 5 * room_of(g, v, learned)) return o;
+    const bool few = early ? learned && r < 0 : r < 0;
+    return B <= (early ? 12 : 6) / (few ? 2 : 1) * room ? o : v;
 }
 KernelFn kernel_fn(const ldpc_graph &g, int v, bool learned) {
     return v >= kNumVariants ? kKernelsOne[learned ? 1 : 0][v - kNumVariants]
