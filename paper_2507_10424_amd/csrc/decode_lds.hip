@@ -490,7 +490,7 @@ int lds_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, uint
     const bool all = cpt <= 8 && g.lds.row_groups <= (g.dc_max > 16 ? 1 : 2) * waves && g.dv_max <= (cpt <= 4 ? 8 : 4);
     LdsFn fn = nullptr;
     size_t lds = 0;
-    int64_t room = 0, promised = 0; // workgroups that the GPU holds
+    int64_t room = 0, promised = 0; // workgroups that the GPU holds, by the runtime's count
     auto choose = [&](int F) {
         // (two frames with rows of up to 16 spill more in the form for all groups:
         // n = 4000, 0.209 ms without it and 0.217 with it)
@@ -508,7 +508,8 @@ int lds_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, uint
     // and 0.143 with two; (4,5) n = 1000, 10,000 frames 1.08 and 0.82); with rows
     // above 8 (whose kernel for two spills) and with four workgroups per CU and
     // more, late (irregular n = 4000: 777 frames 0.180 and 0.256 ms, 6,000 frames
-    // 0.806 and 0.814; (4,8) n = 600: 15,000 frames 0.642 and 0.766; (5,10) n =
+    // 0.806 and 0.814; n = 1200, 256 at once and 512 by the runtime's count, 2,300
+    // frames 0.224 and 0.268, 5,000 frames with two 0.417; (4,8) n = 600: 15,000 frames 0.642 and 0.766; (5,10) n =
     // 1000, 15,000 frames that do not converge: 2.17 and 1.77).  With two or three
     // per CU and short rows, only where the GPU then holds more frames, and all of
     // them or many times as many (rows of at most 8, 20 iterations: n = 1200, two
@@ -518,8 +519,8 @@ int lds_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, uint
     int F = 1;
     const int64_t per_cu = room / g.num_cu;
     const bool few = g.dc_max <= 8 && (per_cu == 2 || per_cu == 3);
-    const int64_t queued = g.dc_max > 8 ? 8 : per_cu >= 4 ? 32 : 1;
-    if (B > queued * room && g.dc_max <= 16 && cpt <= 8 && lds_bytes(g, 2) <= (size_t)g.lds_max) {
+    const int64_t alone = g.dc_max > 8 ? 8 * promised : per_cu >= 4 ? 32 * promised : room; // frames for F = 1
+    if (B > alone && g.dc_max <= 16 && cpt <= 8 && lds_bytes(g, 2) <= (size_t)g.lds_max) {
         const int64_t held = room; // frames, with one per workgroup
         F = 2;
         if (!choose(2)) return LDPC_EHIP;
@@ -529,9 +530,10 @@ int lds_decode(const ldpc_graph &g, const float *llr, int32_t B, int32_t L, uint
         }
     }
     const int64_t groups = ((int64_t)B + F - 1) / F;
-    // (rows of up to 16, n = 600, 800 frames: 0.045 ms with 800 workgroups of which
-    // 768 run at once, 0.062 with 768 and counters for the other 32)
-    const int grid = (int)(groups <= promised ? groups : room);
+    // (workgroups that wait for a CU take it as the first ones end: rows of up to
+    // 16, n = 600, 800 frames 0.045 ms with 800 of which 768 run at once, 0.062 with
+    // 768; n = 700, 1,100 frames 0.134 ms with 768, 0.147 with the 512 that run at once)
+    const int grid = (int)std::min(groups, promised);
     LdsJob J{};
     J.t = LdsTables{g.lds.rows, g.lds.bits, g.lds.row_group, g.lds.bit_group, g.lds.slot_of, g.lds.bit_of,
                     g.lds.row_class, g.lds.row_groups, g.lds.bit_groups, g.lds.npos};
