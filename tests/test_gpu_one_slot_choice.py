@@ -58,6 +58,32 @@ def test_either_side(name, learned):
                               oracle_decode(H, llr.cpu().numpy()[some], L, flags, *(w if learned else ())), f"B={B}")
 
 
+@pytest.mark.parametrize("learned", [False, True])
+@pytest.mark.parametrize("H", [CODES["regular_9_five_waves"], CODES["profile_9_six_waves"],
+                               lambda: wl.regular_ldpc(1530, 765, 3, 6, seed=2)], ids=["regular_9", "profile_9", "six"])
+def test_frames_per_workgroup(H, learned):
+    """3, 5, 6 and 12 frames for each of 256 or 512 workgroups, and one more."""
+    import torch
+    from paper_2507_10424_amd import ldpc
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dev = torch.device("cuda:0")
+    H = H()
+    n, L = H.shape[1], 5
+    g = ldpc.build_graph(torch.from_numpy(H).to(dev))
+    w = [torch.full((L, 1), x, device=dev) for x in (0.8, 0.05)]
+    llr = wl.bpsk_awgn_llr_torch(None, 3.0, 0.6, 4, dev, n=n, batch=3073)
+    for flags in (0, ldpc.LDPC_NO_EARLY_EXIT):
+        run = (lambda x, f: ldpc.nms_decode(g, x, L, *w, flags=f)) if learned else \
+              (lambda x, f: ldpc.minsum_decode(g, x, L, flags=f))
+        ref = run(llr, flags | ldpc.LDPC_FORCE_STREAM)
+        for B in (768, 769, 1536, 1537, 2560, 2561, 3072, 3073):
+            note(f"[frames per workgroup] n={n} B={B} flags={flags} learned={learned}")
+            out = run(llr[:B].contiguous(), flags)
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b[:B]) for a, b in zip(out, ref)), (B, flags)
+
+
 @pytest.mark.parametrize("batches", [(51,), (1638, 51), (1638, 51, 40), (5, 3, 700), (4915, 153, 2457)])
 def test_jobs(batches):
     import torch
